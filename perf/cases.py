@@ -1,0 +1,730 @@
+"""The work whose speed counts, as cases for a timing harness.
+
+A case is a dict of plain values.  `listed()` names the ones that stand for the
+framework's uses, `draw(rng)` gives further ones of the same ranges,
+`prepare(case, seed)` builds what a program holds before the call, `run(state)`
+is one pass through the public entry points, `work(case)` the bytes and
+operations that pass cannot do without, and `exact(case, seed)` its outputs in
+64-bit torch arithmetic written from the method's equations alone.
+
+Kinds of case:
+  step   Sim.step(steps), then the fields a program reads out (n and u, or the
+         layer profiles): every lattice option goes through this
+  batch  Batch.step(steps) on a ragged ensemble, then every slit's profiles
+  force  hslb_force_noalloc on device arrays: the smallest call
+  grad   Trainer.grad: loss and the whole weight gradient of one snapshot
+  net    Sim.surrogate_force: the network's force on the current state
+  learn  Sim.step on the learned-force path (exact judge every 4 steps)
+
+A lattice that stores its populations in FP32 hands its fields on in FP32: the
+read-out arrays are FP64 whatever the storage, and hold no more than that.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_0712_2247_amd import hslb, workloads
+
+T0_39 = 2.0 / 3.0
+
+
+def _slit(nx, ny, height, sigma):
+    w = workloads.wall_layers(sigma)
+    return {"nx": nx, "ny": ny, "nz": height + 2 * w, "walls": w, "sigma": sigma}
+
+
+def _step(name, geo, precision, steps, **kw):
+    c = {"name": name, "kind": "step", **geo, "precision": precision, "steps": steps, "eta": 0.25, "tau": 1.0,
+         "gx": 1e-6, "noise": 0.005, "lattice": 19, "thermal": 0, "attraction": 0.0, "cylinder": 0, "read": "moments"}
+    c.update(kw)
+    return c
+
+
+def _box(nx, ny, nz, sigma):
+    return {"nx": nx, "ny": ny, "nz": nz, "walls": 0, "sigma": sigma}
+
+
+def listed():
+    return [
+        # the smallest lattice in use (tests, the smoke run): launches and latency
+        _step("small slit f64", _slit(8, 8, 20, 4), "f64", 200, gx=1e-5, noise=0.01),
+        # the periodic column of the viscosity sweep, FP64
+        _step("column f64", _box(16, 16, 256, 8), "f64", 200, gx=0.0, shear=1e-4),
+        # liquid-vapour separation with the attraction, FP64
+        _step("coexistence f64", _box(16, 16, 128, 4), "f64", 200, gx=0.0, eta=0.13, attraction=1.2),
+        # the benchmark slit: FP32 storage, resident in the last-level cache
+        _step("slit f32", _slit(64, 64, 128, 8), "f32", 100, tau=0.8, gx=2e-6),
+        # a slit whose rows fit no power of two and whose sigma is odd
+        _step("ragged slit f32", _slit(100, 72, 84, 5), "f32", 100, eta=0.2),
+        # the headline workload: far beyond the caches
+        _step("bulk f32", _box(256, 256, 256, 6), "f32", 20, gx=0.0, noise=0.001, shear=1e-3, read="profiles"),
+        # flow past a solid cylinder (solid mask)
+        _step("obstacle f32", _slit(64, 64, 128, 8), "f32", 100, tau=0.8, gx=2e-6, cylinder=1),
+        # the 39-velocity lattice with the non-isothermal terms, FP64
+        _step("thermal d3q39 f64", _slit(64, 64, 128, 8), "f64", 40, tau=0.8, gx=2e-6, lattice=39, thermal=1,
+              eta=0.12),
+        # the ragged ensemble of slits advanced together
+        {"name": "ensemble f32", "kind": "batch", "nslits": 512, "geometry": 1004, "precision": "f32", "steps": 50},
+        # one force evaluation on device arrays
+        {"name": "force call f64", "kind": "force", **_slit(24, 20, 22, 8), "eta": 0.2, "gx": 1e-5},
+        # forward and backward of the network on one training snapshot
+        {"name": "network gradient", "kind": "grad", **_slit(64, 64, 80, 8), "eta": 0.25},
+        # stepping on the learned force, with its exact judge every 4 steps
+        {"name": "learned run f32", "kind": "learn", **_slit(64, 64, 128, 8), "eta": 0.12, "tau": 0.8, "gx": 2e-6,
+         "noise": 0.005, "steps": 50, "every": 4, "precision": "f32"},
+    ]
+
+
+def _log_int(rng, lo, hi):
+    return int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+
+
+def draw(rng):
+    kind = rng.choice(["step"] * 7 + ["batch", "force", "grad", "net", "learn"])
+    sigma = rng.randint(3, 8)
+    eta = round(rng.uniform(0.10, 0.22), 4)
+    if kind == "batch":
+        return {"kind": "batch", "nslits": _log_int(rng, 24, 512), "geometry": rng.randint(1, 10 ** 6),
+                "precision": rng.choice(["f32", "f32", "f64"]), "steps": rng.randint(10, 50)}
+    if kind == "force":
+        return {"kind": "force", **_slit(rng.randint(12, 40), rng.randint(12, 40), rng.randint(8, 60), sigma),
+                "eta": eta, "gx": 1e-5}
+    if kind in ("grad", "net", "learn"):
+        geo = _slit(32 * rng.randint(1, 3), 4 * rng.randint(4, 24), rng.randint(24, 110), sigma)
+        c = {"kind": kind, **geo, "eta": eta}
+        if kind != "grad":
+            c.update(tau=1.0, gx=1e-6, noise=0.005, precision="f32")
+        if kind == "learn":
+            c.update(steps=rng.randint(20, 60), every=rng.randint(2, 4), eta=round(rng.uniform(0.08, 0.12), 4))
+        return c
+    # lateral sizes: the widths the repository uses and any other
+    nx = rng.choice([8, 16, 32, 64, 64, 128, 256, _log_int(rng, 12, 200), _log_int(rng, 12, 200)])
+    nx = max(nx, sigma + 2)
+    ny = max(sigma + 2, min(256, rng.choice([nx, nx, _log_int(rng, 10, 160)])))
+    most = max(24, min(256, 6_000_000 // (nx * ny)))
+    nz = _log_int(rng, 20, most)
+    form = rng.choice(["plain", "plain", "plain", "plain", "attraction", "cylinder", "d3q39", "thermal"])
+    prec = rng.choice(["f32", "f32", "f64"])
+    if form in ("d3q39", "thermal"):
+        prec = "f64"
+    periodic = rng.random() < 0.3 and form not in ("cylinder",)
+    geo = _box(nx, ny, max(nz, 2 * sigma), sigma) if periodic else _slit(nx, ny, nz, sigma)
+    nodes = geo["nx"] * geo["ny"] * geo["nz"]
+    steps = max(10, min(200, int(60_000_000 / nodes)))
+    big = nodes > 2_000_000
+    kw = dict(eta=eta, tau=round(rng.uniform(0.8, 1.1), 3), gx=0.0 if periodic else 1e-6,
+              read="profiles" if big else "moments")
+    if periodic:
+        kw["shear"] = 1e-3
+    if form == "attraction":
+        kw["attraction"] = round(rng.uniform(0.3, 1.0), 3)
+    if form == "cylinder":
+        kw["cylinder"] = 1
+    if form in ("d3q39", "thermal"):
+        kw.update(lattice=39, thermal=int(form == "thermal"))
+        steps = max(8, steps // 2)
+        kw["eta"] = round(rng.uniform(0.06, 0.12), 4)  # its wall layers stay bounded over long runs up to here
+    c = _step("", geo, prec, steps, **kw)
+    del c["name"]
+    return c
+
+
+# ------------------------------------------------------------------ inputs
+
+
+def _gen(seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(int(seed))
+    return g
+
+
+def _uniform(shape, g):
+    return torch.rand(shape, generator=g, device="cuda", dtype=torch.float64) * 2.0 - 1.0
+
+
+def _fluid(c):
+    """Fluid mask [nz, ny, nx]: between the walls, outside the cylinder (radius
+    min(sigma, nx/4, nz/6), axis along y, at the centre)."""
+    f = torch.zeros((c["nz"], c["ny"], c["nx"]), dtype=torch.bool, device="cuda")
+    f[c["walls"]:c["nz"] - c["walls"]] = True
+    if c.get("cylinder"):
+        r = max(1.0, min(float(c["sigma"]), c["nx"] / 4.0, c["nz"] / 6.0))
+        z = torch.arange(c["nz"], device="cuda", dtype=torch.float64)[:, None, None] - c["nz"] / 2
+        x = torch.arange(c["nx"], device="cuda", dtype=torch.float64)[None, None, :] - c["nx"] / 2
+        f &= ~((z * z + x * x) <= r * r)
+    return f
+
+
+def _attraction(c):
+    """(att_eps, att_range): `attraction` times the critical depth of the
+    mean-field theory, about 0.08 / (n-integral of the well), at range 4."""
+    if not c.get("attraction"):
+        return 0.0, 0.0
+    rng_ = 4.0
+    m = np.arange(-12, 13)
+    g0 = np.exp(-(m / rng_) ** 2).sum() ** 3
+    return float(c["attraction"]) * 10.6 * 2.0 / 3.0 * math.pi * c["sigma"] ** 3 / 6.0 / g0, rng_
+
+
+def _fields(c, seed):
+    """Initial n, u, T on the GPU: the uniform fluid with density noise, a shear
+    wave or (attraction) a density wave; for training states a layered profile."""
+    g = _gen(seed)
+    shape = (c["nz"], c["ny"], c["nx"])
+    nb = 6.0 * c["eta"] / (math.pi * c["sigma"] ** 3)
+    z = torch.arange(c["nz"], device="cuda", dtype=torch.float64)[:, None, None]
+    n = nb * (1.0 + c.get("noise", 0.01) * _uniform(shape, g))
+    if c.get("attraction"):
+        n = n * (1.0 + 0.02 * torch.cos(2.0 * math.pi * z / c["nz"]))
+    if c["kind"] in ("grad", "net"):
+        lo = z - (c["walls"] - 0.5)
+        hi = (c["nz"] - c["walls"] - 0.5) - z
+        for d in (lo, hi):
+            n = n * (1.0 + 0.3 * torch.exp(-d.clamp(min=0.0) / c["sigma"]) * torch.cos(2.0 * math.pi * d / c["sigma"]))
+    u = 1e-4 * _uniform((3,) + shape, g)
+    if c.get("shear"):
+        u[0] += c["shear"] * torch.sin(2.0 * math.pi * z / c["nz"])
+    T = None
+    if c.get("thermal"):
+        T = T0_39 * (1.0 + 0.02 * torch.sin(2.0 * math.pi * z / c["nz"]) + 0.005 * _uniform(shape, g))
+    f = _fluid(c)
+    return n * f, u * f, T, f
+
+
+_CNN = [(32, 1, 125), (32,), (32, 32, 125), (32,), (3, 32, 125), (3,)]
+
+
+def _weights(seed, out_gain=1.0):
+    rng = np.random.default_rng(int(seed) + 77)
+    parts = []
+    for k, shp in enumerate(_CNN):
+        if len(shp) == 1:
+            parts.append(0.05 * rng.standard_normal(shp) * (out_gain if k == 5 else 1.0))
+        else:
+            gain = math.sqrt((2.0 if k < 4 else 1.0) / (shp[1] * shp[2]))
+            parts.append(rng.standard_normal(shp) * gain * (out_gain if k == 4 else 1.0))
+    return np.concatenate([p.ravel() for p in parts]).astype(np.float32)
+
+
+LEARN_GAIN = 0.01  # output layer of the learned run: the network moves the force, the correction carries it
+
+
+def _ensemble(c, seed):
+    """Geometry from the case, packing, field and noise from the seed."""
+    rng = np.random.default_rng(c["geometry"])
+    vals = np.random.default_rng(int(seed) + 5)
+    out = []
+    for s in range(c["nslits"]):
+        h, sigma = int(rng.integers(10, 61)), int(rng.choice([3, 4, 5, 6, 8]))
+        out.append(workloads.slit("s%d" % s, 16, 16, h, sigma, float(vals.uniform(0.10, 0.22)), 1.0,
+                                  float(vals.uniform(1e-6, 1e-5)), 1, c["precision"], 0, 0.0))
+    return out
+
+
+def _ensemble_fields(c, wls, seed):
+    """n of every slit, padded to one shape [slits, nz, 16, 16] (walls and padding 0)."""
+    g = _gen(seed)
+    nz = max(w.nz for w in wls)
+    noise = 1.0 + 0.01 * _uniform((len(wls), nz, 16, 16), g)
+    z = torch.arange(nz, device="cuda")[None, :]
+    lo = torch.tensor([w.wall_lo for w in wls], device="cuda")[:, None]
+    hi = torch.tensor([w.nz - w.wall_hi for w in wls], device="cuda")[:, None]
+    fluid = ((z >= lo) & (z < hi))[:, :, None, None].expand(-1, -1, 16, 16)
+    nb = torch.tensor([w.n_bulk for w in wls], device="cuda", dtype=torch.float64)[:, None, None, None]
+    return nb * noise * fluid, fluid
+
+
+class _State:
+    pass
+
+
+def _host(t):
+    return None if t is None else t.cpu().numpy()
+
+
+def prepare(case, seed):
+    c, s = case, _State()
+    s.case = c
+    s.narrow = c.get("precision") == "f32"
+    if c["kind"] == "batch":
+        wls = _ensemble(c, seed)
+        n, _ = _ensemble_fields(c, wls, seed)
+        n = n.cpu().numpy()
+        s.batch = hslb.Batch(wls, precision=c["precision"])
+        for k, w in enumerate(wls):
+            s.batch.init(k, n[k, :w.nz])
+        s.batch.autotune(steps=10)
+        s.batch.prepare()
+        return s
+    n, u, T, fluid = _fields(c, seed)
+    if c["kind"] == "force":
+        s.n, s.u, s.F = n, u.contiguous(), torch.zeros_like(u)
+        s.params = hslb.make_params(c["nx"], c["ny"], c["nz"], c["sigma"], 1.0, (c["gx"], 0.0, 0.0), c["walls"], c["walls"])
+        return s
+    eps, rng_ = _attraction(c)
+    kw = {}
+    if c["kind"] == "step":
+        kw = dict(att_eps=eps, att_range=rng_, lattice=hslb.HSLB_D3Q39 if c["lattice"] == 39 else hslb.HSLB_D3Q19,
+                  thermal=c["thermal"])
+    if c["kind"] in ("net", "learn"):
+        kw = dict(force_mode=hslb.HSLB_FORCE_SURROGATE, surr_check_every=c.get("every", 50), surr_tol=1e9)
+    s.sim = hslb.Sim(c["nx"], c["ny"], c["nz"], c["sigma"], c.get("tau", 1.0), (c.get("gx", 0.0), 0.0, 0.0),
+                     c["walls"], c["walls"], precision=c.get("precision", "f32"), **kw)
+    if c.get("cylinder"):
+        solid = ~fluid
+        s.sim.set_solid(solid.cpu().numpy())
+    if c["kind"] in ("net", "learn"):
+        hslb.hslb_surrogate_set_weights(s.sim.ctx, _weights(seed, LEARN_GAIN if c["kind"] == "learn" else 1.0))
+    s.sim.init(_host(n), _host(u), _host(T))
+    if c["kind"] == "grad":
+        s.trainer = hslb.Trainer(s.sim.N, s.sim.N)
+        s.trainer.add(s.sim)
+        s.trainer.set_weights(_weights(seed))
+        s.sim.close()
+    elif c["kind"] in ("step", "learn"):
+        s.sim.prepare()
+    return s
+
+
+def run(state):
+    c = state.case
+    kind = c["kind"]
+    if kind == "force":
+        hslb.hslb_force_noalloc(state.params, state.n.data_ptr(), state.u.data_ptr(), state.F.data_ptr(),
+                                torch.cuda.current_stream().cuda_stream)
+        return {"F": state.F}
+    if kind == "batch":
+        state.batch.step(c["steps"])
+        prof = [state.batch.profiles(k) for k in range(c["nslits"])]
+        out = {"n": np.concatenate([p for p, _ in prof]), "u": np.concatenate([v for _, v in prof], axis=1)}
+    elif kind == "grad":
+        loss, g = state.trainer.grad(0)
+        return {"loss": loss, "grad": g}
+    elif kind == "net":
+        out = {"F": state.sim.surrogate_force()}
+    else:
+        state.sim.step(c["steps"])
+        n, u = state.sim.moments() if c.get("read", "moments") == "moments" else state.sim.profiles()
+        out = {"n": n, "u": u}
+    if state.narrow:
+        out = {k: v.astype(np.float32) for k, v in out.items()}
+    return out
+
+
+def work(case):
+    """Step: every population read and written, n and j written and read, once
+    per fluid node and step; about 1000 FP64 operations per node (54 shell
+    elements, collision, moments), twice that with 39 velocities.  Network: the
+    three convolutions (and the two or three products each has backwards)."""
+    c = case
+    if c["kind"] == "batch":
+        nodes = sum(w.fluid_nodes for w in _ensemble(c, 0))
+        size = 4 if c["precision"] == "f32" else 8
+        return {"bytes": float(nodes * c["steps"] * (2 * 19 + 8) * size), "flops": 1000.0 * nodes * c["steps"]}
+    nodes = c["nx"] * c["ny"] * c["nz"]
+    fluid = c["nx"] * c["ny"] * (c["nz"] - 2 * c["walls"])
+    conv = 2.0 * 125 * (32 + 32 * 32 + 32 * 3) * nodes
+    if c["kind"] == "force":
+        return {"bytes": 56.0 * nodes, "flops": 900.0 * fluid}
+    if c["kind"] == "grad":
+        # input, target and gradient; forward, weight gradients, and the input
+        # gradients of layers 2 and 3
+        return {"bytes": 14.0 * nodes + 8.0 * 144067, "flops": 2 * conv + 2.0 * 125 * (32 * 32 + 32 * 3) * nodes}
+    if c["kind"] == "net":
+        return {"bytes": (19 * 4 + 24.0) * nodes, "flops": conv}
+    size, q = (4, 19) if c["precision"] == "f32" else (8, c.get("lattice", 19))
+    t = 1 if c.get("thermal") else 0
+    b = float(fluid) * c["steps"] * (2 * q + 8 + 2 * t) * size
+    if c.get("read", "moments") == "moments":
+        b += 32.0 * nodes
+    fl = 1000.0 * (1 if q == 19 else 2) * fluid * c["steps"]
+    if c["kind"] == "learn":
+        fl += conv * c["steps"]
+    return {"bytes": b, "flops": fl}
+
+
+# ---------------------------------------------------------- 64-bit reference
+
+_C19 = [(0, 0, 0), (1, 0, 0), (-1, 0, 0), (0, 1, 0), (0, -1, 0), (0, 0, 1), (0, 0, -1), (1, 1, 0), (-1, -1, 0),
+        (1, -1, 0), (-1, 1, 0), (1, 0, 1), (-1, 0, -1), (1, 0, -1), (-1, 0, 1), (0, 1, 1), (0, -1, -1), (0, 1, -1),
+        (0, -1, 1)]
+
+
+def _c39():
+    a = [(0, 0, 0)]
+    for k in (1, 2, 3):
+        for ax in range(3):
+            for s in (k, -k):
+                v = [0, 0, 0]
+                v[ax] = s
+                a.append(tuple(v))
+    a += [(x, y, z) for x in (1, -1) for y in (1, -1) for z in (1, -1)]
+    for p, q in ((0, 1), (0, 2), (1, 2)):
+        for s in (2, -2):
+            for t in (2, -2):
+                v = [0, 0, 0]
+                v[p], v[q] = s, t
+                a.append(tuple(v))
+    return a
+
+
+_W39 = {0: 1 / 12, 1: 1 / 12, 3: 1 / 27, 4: 2 / 135, 8: 1 / 432, 9: 1 / 1620}
+
+
+def _at(a, d):
+    """a(r + d) on [..., z, y, x], periodic."""
+    return torch.roll(a, (-d[2], -d[1], -d[0]), (-3, -2, -1)) if any(d) else a
+
+
+def _shell(sigma):
+    """(W, s, [(alpha, d), ...]) of the 18 quadrature points."""
+    out = []
+    for ax in range(3):
+        for s in (1, -1):
+            v, d = [0.0] * 3, [0] * 3
+            v[ax], d[ax] = float(s), s * sigma
+            out.append((1 / 30, tuple(v), [(1.0, tuple(d))]))
+    big = sigma / math.sqrt(2.0)
+    lo = math.floor(big)
+    th = big - lo
+    for a, b in ((0, 1), (0, 2), (1, 2)):
+        for sa in (1, -1):
+            for sb in (1, -1):
+                v = [0.0] * 3
+                v[a], v[b] = sa / math.sqrt(2.0), sb / math.sqrt(2.0)
+                cs = []
+                for ia in (0, 1):
+                    for ib in (0, 1):
+                        d = [0] * 3
+                        d[a], d[b] = sa * (lo + ia), sb * (lo + ib)
+                        cs.append(((th if ia else 1 - th) * (th if ib else 1 - th), tuple(d)))
+                out.append((1 / 15, tuple(v), cs))
+    return out
+
+
+class _Exact:
+    """The step on fields [..., nz, ny, nx] in FP64.  `fluid`: mask; `chi`: wall
+    factor; walls at z = lo and nz - hi (39 velocities only); padding layers
+    keep fields from wrapping in z where `zper` is false."""
+
+    def __init__(self, fluid, zper, sigma, tau, g, chi, lattice=19, thermal=0, eps=0.0, rng_=0.0, walls=0):
+        self.fluid, self.zper, self.sigma, self.tau, self.g, self.chi = fluid, zper, sigma, tau, g, chi
+        self.pad = 0 if zper else sigma + 1
+        self.c = _C19 if lattice == 19 else _c39()
+        self.cs2 = 1 / 3 if lattice == 19 else T0_39
+        self.w = [(1 / 3, 1 / 18, 1 / 36)[sum(x * x for x in v)] if lattice == 19 else _W39[sum(x * x for x in v)]
+                  for v in self.c]
+        self.opp = [self.c.index(tuple(-x for x in v)) for v in self.c]
+        self.thermal, self.walls = thermal, walls
+        self.shell = _shell(sigma)
+        r = sigma // 2
+        self.ball = [(x, y, z) for z in range(-r, r + 1) for y in range(-r, r + 1) for x in range(-r, r + 1)
+                     if 4 * (x * x + y * y + z * z) <= sigma * sigma]
+        self.eps, self.range = eps, rng_
+        self.f = None
+
+    def feq(self, i, n, u, T):
+        v, cs2 = self.c[i], self.cs2
+        cu = (v[0] * u[0] + v[1] * u[1] + v[2] * u[2]) / cs2
+        uu = (u[0] * u[0] + u[1] * u[1] + u[2] * u[2]) / cs2
+        if len(self.c) == 19:
+            return self.w[i] * n * (1 + cu + 0.5 * cu * cu - 0.5 * uu)
+        xx = sum(x * x for x in v) / cs2
+        th = T / cs2 - 1 if self.thermal else 0.0
+        return self.w[i] * n * (1 + cu + 0.5 * (cu * cu - uu + th * (xx - 3)) +
+                                cu * (cu * cu - 3 * uu + 3 * th * (xx - 5)) / 6)
+
+    def init(self, n, u, T=None):
+        T = torch.full_like(n, self.cs2) if T is None else T
+        self.f = [self.feq(i, n, u, T) * self.fluid for i in range(len(self.c))]
+
+    def moments(self):
+        n = sum(self.f)
+        j = [sum(v[a] * f for v, f in zip(self.c, self.f) if v[a]) for a in range(3)]
+        inv = torch.where(n != 0, 1 / torch.where(n != 0, n, torch.ones_like(n)), torch.zeros_like(n))
+        u = [x * inv for x in j]
+        T = None
+        if self.thermal:
+            e = sum(sum(x * x for x in v) * f for v, f in zip(self.c, self.f))
+            T = (e * inv - sum(x * x for x in u)) / 3
+        return n, j, u, T
+
+    def _z(self, a):
+        return a if self.zper else torch.nn.functional.pad(a, (0, 0, 0, 0, self.pad, self.pad))
+
+    def _cut(self, a):
+        return a if self.zper else a[..., self.pad:a.shape[-3] - self.pad, :, :]
+
+    def force(self, n, j, u, T):
+        """C1 (no external field) and the thermal energy source."""
+        sg = self.sigma
+        z = self._z
+        n_, j_ = z(n), [z(x) for x in j]
+        T_ = z(T) if self.thermal else None
+        eb = sum(_at(n_, o) for o in self.ball) * (math.pi * sg ** 3 / 6 / len(self.ball))
+        g2 = {}
+
+        def contact(d):
+            par = tuple(x & 1 for x in d)
+            if par not in g2:
+                e, k = 0, 0
+                for x in range(par[0] + 1):
+                    for y in range(par[1] + 1):
+                        for zz in range(par[2] + 1):
+                            e, k = e + _at(eb, (x, y, zz)), k + 1
+                e = e / k
+                g2[par] = (1 - e / 2 + e * e / 4) / (1 - e) ** 3
+            return _at(g2[par], tuple((x - (x & 1)) // 2 for x in d))
+
+        S = [torch.zeros_like(n) for _ in range(3)]
+        Q = torch.zeros_like(n)
+        vt2 = T if self.thermal else self.cs2
+        vt = torch.sqrt(T.clamp(min=1e-300)) if self.thermal else math.sqrt(self.cs2)
+        kap = 2 / (vt * math.sqrt(math.pi))
+        for W, s, corners in self.shell:
+            su = sum(s[a] * u[a] for a in range(3) if s[a])
+            acc = torch.zeros_like(n)
+            for al, d in corners:
+                G = self._cut(contact(d))
+                n2 = self._cut(_at(n_, d))
+                cur = sum(s[a] * self._cut(_at(j_[a], d)) for a in range(3) if s[a]) - n2 * su
+                el = n2 - self.chi * kap * cur
+                if self.thermal:
+                    ndT = n2 * (self._cut(_at(T_, d)) - T)
+                    el = el + ndT / (2 * T.clamp(min=1e-300))
+                    Q += W * al * G * (-0.5 * cur + ndT / (math.sqrt(math.pi) * vt))
+                acc += al * G * el
+            for a in range(3):
+                if s[a]:
+                    S[a] += W * s[a] * acc
+        pre = -vt2 * sg * sg * 4 * math.pi * n
+        F = [pre * x for x in S]
+        if self.eps:
+            R = math.ceil(3 * self.range)
+            p = n if self.zper else torch.nn.functional.pad(n, (0, 0, 0, 0, R, R))
+            for ax in range(3):
+                o = [0, 0, 0]
+                acc = torch.zeros_like(p)
+                for m in range(-R, R + 1):
+                    o[ax] = m
+                    acc += math.exp(-(m / self.range) ** 2) * _at(p, o)
+                p = acc
+            phi = -self.eps * (p if self.zper else p[..., R:p.shape[-3] - R, :, :])
+            for ax in range(3):
+                o = [0, 0, 0]
+                o[ax] = 1
+                F[ax] = F[ax] - n * (_at(phi, o) - _at(phi, [-x for x in o])) / 2
+        return [x * self.fluid for x in F], -pre * Q
+
+    def collide(self, n, u, T, F, Q):
+        om = 1 / self.tau
+        cs2 = self.cs2
+        feq = [self.feq(i, n, u, T) for i in range(len(self.c))]
+        cF = [sum(v[a] * F[a] for a in range(3) if v[a]) if any(v) else torch.zeros_like(n) for v in self.c]
+        if len(self.c) == 19:
+            return [f - om * (f - e) + w / cs2 * x for f, e, w, x in zip(self.f, feq, self.w, cF)]
+        neq = [f - e for f, e in zip(self.f, feq)]
+        ax3 = [(a, b) for a in range(3) for b in range(3)]
+        h2 = lambda v, a, b: v[a] * v[b] - (cs2 if a == b else 0.0)  # noqa: E731
+        h3 = lambda v, a, b, g: v[a] * v[b] * v[g] - cs2 * (v[a] * (b == g) + v[b] * (a == g) + v[g] * (a == b))  # noqa: E731
+        s2 = [(a, b) for a, b in ax3 if a <= b]
+        s3 = [(a, b, g) for a in range(3) for b in range(a, 3) for g in range(b, 3)]
+        a2 = {k: sum(h2(v, *k) * x for v, x in zip(self.c, neq) if h2(v, *k)) for k in s2}
+        a3 = {k: sum(h3(v, *k) * x for v, x in zip(self.c, neq) if h3(v, *k)) for k in s3}
+        mult = lambda k: math.factorial(len(k)) // math.prod(math.factorial(k.count(q)) for q in set(k))  # noqa: E731
+        Fu = sum(F[a] * u[a] for a in range(3))
+        out = []
+        for i, v in enumerate(self.c):
+            p2 = sum(mult(k) * h2(v, *k) * a2[k] for k in s2)
+            p3 = sum(mult(k) * h3(v, *k) * a3[k] for k in s3)
+            src = cF[i] / cs2
+            if self.thermal:
+                cu = sum(v[a] * u[a] for a in range(3))
+                src = src + (cF[i] * cu - cs2 * Fu) / cs2 ** 2 + Q * (sum(x * x for x in v) - 3 * cs2) / (3 * cs2 ** 2)
+            out.append(feq[i] + (1 - om) * self.w[i] * (p2 / (2 * cs2 ** 2) + p3 / (6 * cs2 ** 3)) + self.w[i] * src)
+        return out
+
+    def stream(self, post):
+        new = [torch.zeros_like(p) for p in post]
+        for i, v in enumerate(self.c):
+            back = tuple(-x for x in v)
+            if len(self.c) == 19 or self.zper:
+                src_fluid = _at(self.fluid, back)
+                got = _at(post[i], back)
+                new[i] = torch.where(self.fluid & src_fluid, got, new[i])
+                hit = self.fluid & ~_at(self.fluid, v)  # the link out of r along v meets a solid node
+                new[self.opp[i]] = torch.where(hit, post[i], new[self.opp[i]])
+                continue
+            lo, hi = self.walls, self.fluid.shape[-3] - self.walls
+            for z in range(lo, hi):
+                zt, dx, dy, k = z + v[2], v[0], v[1], i
+                if zt < lo or zt >= hi:
+                    d = z - lo if zt < lo else hi - 1 - z
+                    go = 2 * d + 1 - abs(v[2])
+                    dx, dy, k = v[0] // abs(v[2]) * go, v[1] // abs(v[2]) * go, self.opp[i]
+                    zt = 2 * lo - 1 - zt if zt < lo else 2 * hi - 1 - zt
+                new[k][zt] = torch.roll(post[i][z], (dy, dx), (-2, -1))
+        self.f = new
+
+    def step(self, steps, force=None):
+        for t in range(steps):
+            n, j, u, T = self.moments()
+            F, Q = (force or (lambda t, n, j, u, T: self.force(n, j, u, T)))(t, n, j, u, T)
+            F = [F[a] + n * self.g[a] for a in range(3)]
+            self.stream([p * self.fluid for p in self.collide(n, u, T, F, Q)])
+
+
+def _chi(c, fluid):
+    """1 - exp(-d / sigma): d to the wall plane, or to the nearest solid node less half a spacing."""
+    if fluid.all():
+        return torch.ones(fluid.shape, dtype=torch.float64, device=fluid.device)
+    nz, ny, nx = fluid.shape
+    z = torch.arange(nz, device=fluid.device, dtype=torch.float64)
+    d2 = torch.full((nz, nx), 1e30, dtype=torch.float64, device=fluid.device)
+    if c["walls"]:
+        d2 = torch.minimum(z - (c["walls"] - 1), nz - c["walls"] - z)[:, None].square().expand(nz, nx).clone()
+    solid = ~fluid[:, 0, :]  # the same for every y
+    solid[:c["walls"]] = False
+    solid[nz - c["walls"]:] = False
+    x = torch.arange(nx, device=fluid.device, dtype=torch.float64)
+    for zs, xs in solid.nonzero().tolist():
+        dx = (x - xs).abs()
+        dx = torch.minimum(dx, nx - dx)
+        d2 = torch.minimum(d2, (z - zs).square()[:, None] + dx.square()[None, :])
+    chi = 1 - torch.exp(-(d2.sqrt() - 0.5) / c["sigma"])
+    return chi[:, None, :].expand(nz, ny, nx).contiguous()
+
+
+def _taps(zper, a):
+    """a [N3.., C] at r + t for the 125 taps, zero beyond walled ends in z."""
+    nz = a.shape[0]
+    b = a if zper else torch.nn.functional.pad(a, (0, 0, 0, 0, 0, 0, 2, 2))
+    for t in range(125):
+        dz, dy, dx = t // 25 - 2, (t // 5) % 5 - 2, t % 5 - 2
+        v = torch.roll(b, (-dy, -dx), (1, 2)) if dx or dy else b
+        yield t, (torch.roll(v, -dz, 0) if zper else v[2 + dz:2 + dz + nz])
+
+
+def _conv(zper, a, w, b):
+    """a [nz, ny, nx, ci], w [co, ci, 125]."""
+    out = b.expand(a.shape[:3] + (w.shape[0],)).clone()
+    for t, v in _taps(zper, a):
+        out += v @ w[:, :, t].T
+    return out
+
+
+def _conv_t(zper, g, w):
+    """The transposed convolution of g [.., co]."""
+    return _conv(zper, g, w.permute(1, 0, 2).flip(2), torch.zeros(w.shape[1], dtype=g.dtype, device=g.device))
+
+
+def _wgrad(zper, a, g):
+    gw = torch.zeros((g.shape[-1], a.shape[-1], 125), dtype=g.dtype, device=g.device)
+    gf = g.reshape(-1, g.shape[-1]).T
+    for t, v in _taps(zper, a):
+        gw[:, :, t] = gf @ v.reshape(-1, a.shape[-1])
+    return gw
+
+
+def _split(w):
+    w = torch.from_numpy(w).to("cuda", torch.float64)
+    parts, k = [], 0
+    for shp in _CNN:
+        m = math.prod(shp)
+        parts.append(w[k:k + m].reshape(shp))
+        k += m
+    return parts
+
+
+def _cdf(z):
+    return 0.5 * torch.erfc(-z / math.sqrt(2.0))
+
+
+def _net(zper, x, w):
+    z1 = _conv(zper, x[..., None], w[0], w[1])
+    a1 = z1 * _cdf(z1)
+    z2 = _conv(zper, a1, w[2], w[3])
+    a2 = z2 * _cdf(z2)
+    return z1, a1, z2, a2, _conv(zper, a2, w[4], w[5])
+
+
+def _lattice(c, fluid):
+    eps, rng_ = _attraction(c)
+    return _Exact(fluid, c["walls"] == 0, c["sigma"], c.get("tau", 1.0), (c.get("gx", 0.0), 0.0, 0.0), _chi(c, fluid),
+                  c.get("lattice", 19), c.get("thermal", 0), eps, rng_, c["walls"])
+
+
+def exact(case, seed):
+    c = case
+    if c["kind"] == "batch":
+        wls = _ensemble(c, seed)
+        n_all, fluid_all = _ensemble_fields(c, wls, seed)
+        got = [None] * len(wls)
+        for sigma in sorted({w.sigma for w in wls}):
+            ks = [k for k, w in enumerate(wls) if w.sigma == sigma]
+            idx = torch.tensor(ks, device="cuda")
+            n, fluid = n_all[idx], fluid_all[idx].contiguous()
+            z = torch.arange(n.shape[1], device="cuda", dtype=torch.float64)[None, :]
+            lo = torch.tensor([wls[k].wall_lo - 0.5 for k in ks], device="cuda", dtype=torch.float64)[:, None]
+            hi = torch.tensor([wls[k].nz - wls[k].wall_hi - 0.5 for k in ks], device="cuda", dtype=torch.float64)[:, None]
+            chi = (1 - torch.exp(-torch.minimum(z - lo, hi - z).clamp(min=0.0) / sigma))[:, :, None, None]
+            gx = torch.tensor([wls[k].accel[0] for k in ks], device="cuda", dtype=torch.float64)[:, None, None, None]
+            e = _Exact(fluid, False, sigma, 1.0, (gx, 0.0, 0.0), chi)
+            e.init(n, [torch.zeros_like(n)] * 3)
+            e.step(c["steps"])
+            n, j, _, _ = e.moments()
+            sn = n.sum((-2, -1))
+            inv = torch.where(sn != 0, 1 / torch.where(sn != 0, sn, torch.ones_like(sn)), torch.zeros_like(sn))
+            u = torch.stack([x.sum((-2, -1)) * inv for x in j])
+            for q, k in enumerate(ks):
+                got[k] = ((sn / 256.0)[q, :wls[k].nz].cpu().numpy(), u[:, q, :wls[k].nz].cpu().numpy())
+        return {"n": np.concatenate([p for p, _ in got]), "u": np.concatenate([v for _, v in got], axis=1)}
+    n, u, T, fluid = _fields(c, seed)
+    e = _lattice(c, fluid)
+    zper = c["walls"] == 0
+    e.init(n, list(u), T)
+    if c["kind"] == "force":
+        F, _ = e.force(*e.moments())
+        return {"F": torch.stack([F[a] + n * e.g[a] for a in range(3)])}
+    fs = (1 / 3) * (6 / math.pi) ** 2 * 4 * math.pi / c["sigma"] ** 4
+    eta = math.pi * c["sigma"] ** 3 / 6
+    if c["kind"] == "grad":
+        w = _split(_weights(seed))
+        x = eta * n
+        F, _ = e.force(*e.moments())
+        z1, a1, z2, a2, out = _net(zper, x, w)
+        d = (out - torch.stack(F, -1) / fs) * fluid[..., None]
+        count = 3.0 * float(fluid.sum())
+        g3 = 2 * d / count
+        dact = lambda z: _cdf(z) + z * torch.exp(-0.5 * z * z) / math.sqrt(2 * math.pi)  # noqa: E731
+        g2 = _conv_t(zper, g3, w[4]) * dact(z2)
+        g1 = _conv_t(zper, g2, w[2]) * dact(z1)
+        parts = []
+        for a, g in ((x[..., None], g1), (a1, g2), (a2, g3)):
+            parts += [_wgrad(zper, a, g).ravel(), g.sum((0, 1, 2))]
+        return {"loss": float((d * d).sum() / count), "grad": torch.cat(parts).cpu().numpy()}
+    if c["kind"] == "net":
+        out = _net(zper, eta * n, _split(_weights(seed)))[-1]
+        return {"F": (fs * out.permute(3, 0, 1, 2)).cpu().numpy()}
+    if c["kind"] == "learn":
+        w, keep = _split(_weights(seed, LEARN_GAIN)), {}
+
+        def force(t, n, j, u, T):
+            hat = fs * _net(zper, eta * n, w)[-1].permute(3, 0, 1, 2) * fluid
+            if t % c["every"] == 0:
+                F, _ = e.force(n, j, u, T)
+                keep["delta"] = torch.stack(F) - hat
+                return F, None
+            return list(hat + keep["delta"]), None
+
+        e.step(c["steps"], force)
+    else:
+        e.step(c["steps"])
+    n, j, u, _ = e.moments()
+    if c.get("read", "moments") == "moments":
+        return {"n": n.cpu().numpy(), "u": torch.stack(u).cpu().numpy()}
+    sn = n.sum((-2, -1))
+    inv = torch.where(sn != 0, 1 / torch.where(sn != 0, sn, torch.ones_like(sn)), torch.zeros_like(sn))
+    plane = c["nx"] * c["ny"]
+    return {"n": (sn / plane).cpu().numpy(), "u": torch.stack([x.sum((-2, -1)) * inv for x in j]).cpu().numpy()}
