@@ -91,6 +91,8 @@ def draw(rng):
         return {"kind": "force", **_slit(rng.randint(12, 40), rng.randint(12, 40), rng.randint(8, 60), sigma),
                 "eta": eta, "gx": 1e-5}
     if kind in ("grad", "net", "learn"):
+        if kind == "learn":  # below, the stand-in network's force outgrows what its correction holds stable
+            sigma = max(sigma, 5)
         geo = _slit(32 * rng.randint(1, 3), 4 * rng.randint(4, 24), rng.randint(24, 110), sigma)
         c = {"kind": kind, **geo, "eta": eta}
         if kind != "grad":
