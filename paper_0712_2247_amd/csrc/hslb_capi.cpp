@@ -620,7 +620,17 @@ public:
     {
         int rc;
         if (l39()) return one_step39();
-        if (sc_.hs_on && fused_rows()) {
+        const bool split = collide_split_apply(L_, sigma_, sc_, sizeof(TM));
+        const bool small = split && fields_small_apply(L_, sigma_, sizeof(TM));
+        const AttWeights *aw = sc_.phi ? &aw_ : nullptr;
+        double *att_b = sc_.phi ? att_d_ + (size_t)L_.N : nullptr;
+        if (small) {
+            rc = launch("fields", [&] {
+                return launch_fields_small<TF, TM>(st(), L_, sigma_, sc_.eta_pref, sc_.g2_model, nref_d_, f_[cur_], fld_,
+                                                   aw, att_b);
+            });
+            if (rc) return rc;
+        } else if (sc_.hs_on && fused_rows()) {
             rc = launch("moments", [&] {
                 return launch_moments_rs<TF, TM>(st(), L_, sigma_, nref_d_, f_[cur_], fld_, rs_, sc_.phi != nullptr);
             });
@@ -634,8 +644,10 @@ public:
             if (rc) return rc;
             if (sc_.hs_on && (rc = fields_hs())) return rc;
         }
-        if (sc_.phi && (rc = attraction())) return rc;
+        if (sc_.phi && !small && (rc = attraction())) return rc;
         rc = launch("collide", [&] {
+            if (split) return launch_collide_split<TF, TM>(st(), L_, sigma_, sc_, chi_d_, f_[cur_], f_[1 - cur_], fld_, aw,
+                                                           att_b);
             return launch_collide<TF, TM>(st(), L_, sigma_, sc_, chi_d_, f_[cur_], f_[1 - cur_], fld_, collide_tiles);
         });
         if (rc) return rc;
@@ -2578,6 +2590,11 @@ int hslb_force_noalloc(const hslb_params *p, const double *n, const double *u, d
         hipError_t e_ = (__VA_ARGS__);                                                                     \
         if (e_ != hipSuccess) return fail(err, HSLB_EDEVICE, "%s: %s", #__VA_ARGS__, hipGetErrorString(e_)); \
     } while (0)
+    if (sc.hs_on && force_fields_apply(L, sig)) {
+        // the moments of the local equilibrium are (n, n u) themselves
+        NA_TRY(launch_force_fields(s, L, sig, p->wall_reg, sc, d + o_chi, n, u, fld, F));
+        return HSLB_OK;
+    }
     NA_TRY(launch_fill(s, d + o_ref, (size_t)NQ * p->nz, 0.0));
     NA_TRY(launch_fill(s, fld.n, nfld, 0.0));
     NA_TRY(launch_chi(s, L, sig, p->wall_reg, d + o_chi));

@@ -169,6 +169,28 @@ template <typename TM>
 hipError_t launch_smooth2(hipStream_t s, const LatticeDev &L, int sigma, double eta_pref, Fields<TM> fld,
                           TM *rs);
 
+// Small lattices in two launches per step: every field of the shell sum (the
+// moments, the ball sum and the contact values; eta_bar itself is not written),
+// then the collision with the shell sum split over six waves.  With the
+// attraction (aw not null) the first also forms the passes along x and y of the
+// potential in att_b [N] and the density field fld.n, and the second its pass
+// along z.  The *_apply rules say which lattices they take; the launchers
+// return hipErrorInvalidValue for others.
+bool fields_small_apply(const LatticeDev &L, int sigma, size_t tm_bytes);
+bool collide_split_apply(const LatticeDev &L, int sigma, const StepConst &c, size_t tm_bytes);
+bool force_fields_apply(const LatticeDev &L, int sigma);
+template <typename TF, typename TM>
+hipError_t launch_fields_small(hipStream_t s, const LatticeDev &L, int sigma, double eta_pref, int g2_model,
+                               const double *nref, const TF *f, Fields<TM> fld, const AttWeights *aw, double *att_b);
+template <typename TF, typename TM>
+hipError_t launch_collide_split(hipStream_t s, const LatticeDev &L, int sigma, const StepConst &c, const double *chi,
+                                const TF *fin, TF *fout, Fields<TM> fld, const AttWeights *aw, const double *att_b);
+// The force F[3][N] of the fields n[N] and u[3][N] (null: rest) with the same
+// two kernels, without populations (force_fields_apply lattices).  Nothing of
+// fld and chi[nz] needs to be set or cleared before.
+hipError_t launch_force_fields(hipStream_t s, const LatticeDev &L, int sigma, int wall_reg, const StepConst &c, double *chi,
+                               const double *n, const double *u, Fields<double> fld, double *F);
+
 // tiles: with FP32 storage and fields, nx a multiple of 64 and ny of 4, no
 // solid mask, the hard-sphere force on and sigma in 2..8, the collide stages
 // shell fields of each 64 x 4 tile through LDS (bit for bit the same result).

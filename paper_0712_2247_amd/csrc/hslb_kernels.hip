@@ -855,7 +855,7 @@ struct GlobalShell {
 // The interpolated quadrature point q = (SA, SB) in plane PL and its mirror -q:
 // W s_q sum_k alpha_k (e+_k - e-_k), k over the four bilinear corners.
 template <int PL, int SA, int SB, int LL, typename SRC, typename TC>
-__device__ __forceinline__ void diag_pair(const SRC &src, const NodeCtx<TC> &c, const TC *alpha, TC S[3])
+__device__ __forceinline__ TC diag_pair_sum(const SRC &src, const NodeCtx<TC> &c, const TC *alpha)
 {
     constexpr int A = (PL == 2) ? 1 : 0;
     constexpr int B = (PL == 0) ? 1 : 2;
@@ -883,7 +883,15 @@ __device__ __forceinline__ void diag_pair(const SRC &src, const NodeCtx<TC> &c, 
         d += alpha[2] * src.template elem<D10::DX, D10::DY, D10::DZ, D10::SX, D10::SY, D10::SZ, true>(c, su);
         d += alpha[3] * src.template elem<D11::DX, D11::DY, D11::DZ, D11::SX, D11::SY, D11::SZ, true>(c, su);
     }
-    const TC w = TC((1.0 / 15.0) * 0.70710678118654752440) * d;
+    return d;
+}
+
+template <int PL, int SA, int SB, int LL, typename SRC, typename TC>
+__device__ __forceinline__ void diag_pair(const SRC &src, const NodeCtx<TC> &c, const TC *alpha, TC S[3])
+{
+    constexpr int A = (PL == 2) ? 1 : 0;
+    constexpr int B = (PL == 0) ? 1 : 2;
+    const TC w = TC((1.0 / 15.0) * 0.70710678118654752440) * diag_pair_sum<PL, SA, SB, LL>(src, c, alpha);
     S[A] += TC(SA) * w;
     S[B] += TC(SB) * w;
 }
@@ -1509,6 +1517,586 @@ __global__ __launch_bounds__(256) void k_force(LatticeDev L, StepConst sc, const
     Fout[id] = Fv[0];
     Fout[L.N + id] = Fv[1];
     Fout[2 * (size_t)L.N + id] = Fv[2];
+}
+
+// ------------------------------------------------------------ small lattices
+//
+// A lattice of a few thousand nodes leaves the chip idle: its step is bound by
+// the number of launches (2 us each at the least) and by the chain of memory
+// round trips inside a wave, not by bandwidth.  Two kernels replace the five:
+//   k_fields_small   moments, ball sum and contact values of one layer per
+//                    block; the moments of the R + R + 1 layers around it, whose
+//                    densities the ball sums read, are formed again by every
+//                    block that needs them and kept in LDS;
+//   k_collide_split  64 nodes per block, six waves: each takes one face-diagonal
+//                    point of the shell (and three of them an axis pair), then
+//                    three or four of the 19 directions.  A wave then waits for
+//                    about 30 loads instead of 127.
+// Every sum is formed in the order of the general kernels, so the results are
+// bit for bit theirs.
+
+// Sources of the density and current of a node: stored populations with their
+// reference table, or the fields (n, u) themselves (the rest state without u;
+// the fields kernel then also writes the wall factors and clears the padding,
+// since the caller's scratch holds an earlier call's contents).
+template <typename TF>
+struct PopSource {
+    const TF *f;
+    const double *nref;
+};
+struct FieldSource {
+    const double *n, *u;
+    double *chi;
+    int wall_reg;
+};
+
+// Wall factor 1 - exp(-d_w / sigma) of layer z (1 without walls or wall_reg).
+__device__ __forceinline__ double wall_factor(const LatticeDev &L, int sigma, int wall_reg, int z)
+{
+    if (L.zper || !wall_reg) return 1.0;
+    const double za = L.wall_lo - 0.5, zb = L.nz - L.wall_hi - 0.5;
+    return 1.0 - exp(-fmin((double)z - za, zb - (double)z) / (double)sigma);
+}
+
+// What a source loads for node r of layer z, and the moments formed from it.
+// `own`: the node's current is wanted too (the halo layers give densities only).
+template <typename TF>
+struct PopNode {
+    static constexpr int BATCH = 2;  // nodes a lane loads at a time
+    TF f[NQ];
+    const double *rf;
+    __device__ __forceinline__ void load(const LatticeDev &L, const PopSource<TF> &src, int z, int r, bool)
+    {
+        const int id = z * L.plane + r;
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) f[i] = src.f[(size_t)i * L.pop_stride + id];
+        rf = layer_ref(src.nref, z);
+    }
+    __device__ __forceinline__ void moments(double &n, double j[3]) const
+    {
+        n = j[0] = j[1] = j[2] = 0.0;
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const double fi = (double)f[i] + rf[i];
+            n += fi;
+            if (CX[i] > 0) j[0] += fi;
+            if (CX[i] < 0) j[0] -= fi;
+            if (CY[i] > 0) j[1] += fi;
+            if (CY[i] < 0) j[1] -= fi;
+            if (CZ[i] > 0) j[2] += fi;
+            if (CZ[i] < 0) j[2] -= fi;
+        }
+    }
+};
+struct FieldNode {
+    static constexpr int BATCH = 4;
+    double n_, u_[3];
+    __device__ __forceinline__ void load(const LatticeDev &L, const FieldSource &src, int z, int r, bool own)
+    {
+        const int id = z * L.plane + r;
+        n_ = src.n[id];
+        u_[0] = u_[1] = u_[2] = 0.0;
+        if (own && src.u) {
+#pragma unroll
+            for (int a = 0; a < 3; ++a) u_[a] = src.u[(size_t)a * L.N + id];
+        }
+    }
+    __device__ __forceinline__ void moments(double &n, double j[3]) const
+    {
+        n = n_;
+#pragma unroll
+        for (int a = 0; a < 3; ++a) j[a] = n_ * u_[a];
+    }
+};
+template <typename SRC>
+struct NodeOf;
+template <typename TF>
+struct NodeOf<PopSource<TF>> {
+    using type = PopNode<TF>;
+};
+template <>
+struct NodeOf<FieldSource> {
+    using type = FieldNode;
+};
+
+// The row sums that the ball sums of two neighbouring layers read.  Those of
+// half-width w are kept for the layers within reach[w] of either layer (the
+// ball narrows away from its middle; all of them for w = 0, the densities), at
+// base[w] + layer; at[oy + R][oz + R] is where the ball's row (oy, oz) of the
+// lower layer lies, or -1.  Tables, so that the unrolled loops hold constants.
+template <int SIG>
+struct BallRows {
+    static constexpr int R = SIG / 2;
+    int reach[R + 1] = {}, layers[R + 1] = {}, base[R + 2] = {}, at[2 * R + 1][2 * R + 1] = {};
+    constexpr BallRows()
+    {
+        for (int oz = 0; oz <= R; ++oz)
+            for (int oy = 0; oy <= R; ++oy) {
+                const int rem2 = SIG * SIG - 4 * (oy * oy + oz * oz);
+                if (rem2 >= 0 && oz > reach[isqrt_floor(rem2 / 4)]) reach[isqrt_floor(rem2 / 4)] = oz;
+            }
+        reach[0] = R;
+        for (int w = 0; w <= R; ++w) {
+            layers[w] = 2 * reach[w] + 2;
+            base[w + 1] = base[w] + layers[w];
+        }
+        for (int oy = -R; oy <= R; ++oy)
+            for (int oz = -R; oz <= R; ++oz) {
+                const int rem2 = SIG * SIG - 4 * (oy * oy + oz * oz);
+                const int w = rem2 >= 0 ? isqrt_floor(rem2 / 4) : 0;
+                at[oy + R][oz + R] = rem2 >= 0 ? base[w] + reach[w] + oz : -1;
+            }
+    }
+};
+template <int SIG>
+constexpr int ball_row_layers() { return BallRows<SIG>().base[SIG / 2 + 1]; }
+__host__ __device__ constexpr int ball_row_layers_of(int sigma)
+{
+    switch (sigma) {
+    case 2: return ball_row_layers<2>();
+    case 3: return ball_row_layers<3>();
+    case 4: return ball_row_layers<4>();
+    case 5: return ball_row_layers<5>();
+    case 6: return ball_row_layers<6>();
+    case 7: return ball_row_layers<7>();
+    default: return ball_row_layers<8>();
+    }
+}
+
+// Tiling of k_fields_small: `bands` blocks per layer, `ty` rows each; with one
+// band the block holds the whole (periodic) layer, otherwise `rows` = ty + 1
+// rows of eta_bar and R more on either side.  magic: floor(v / nx) =
+// umulhi(v, magic) for v below 2^16.
+struct SmallTile {
+    int bands, ty, rows;
+    uint32_t magic;
+};
+
+// LDS of k_fields_small in bytes: the row sums (w = 0: the densities), eta_bar
+// of two layers, and the x-pass of the attraction.
+__host__ __device__ constexpr size_t fields_small_lds(int sigma, int nodes, size_t tm)
+{
+    return (size_t)nodes * (tm * (size_t)(ball_row_layers_of(sigma) + 2) + sizeof(double));
+}
+
+// Fields of `ty` rows of one layer: (n, j) and the contact values, with their
+// periodic images (eta_bar stays in LDS: within a step only the contact values
+// read it).  ATT (one band): also the attraction's passes along x and y, into
+// att_b.  Waves take (layer, 64 nodes) items, so that a layer's reference rows
+// are scalar loads and the index arithmetic is scalar but for one row number.
+template <int SIG, typename SRC, typename TM, bool ATT>
+__global__ __launch_bounds__(1024) void k_fields_small(LatticeDev L, SRC src, Fields<TM> fld, double eta_pref,
+                                                       int g2_model, SmallTile st, AttWeights aw,
+                                                       double *__restrict__ att_b)
+{
+    constexpr int R = SIG / 2, NL = 2 * R + 2;
+    extern __shared__ __attribute__((aligned(16))) unsigned char s_raw[];
+    const int nx = L.nx, P = st.rows * nx;
+    double *s_att = (double *)s_raw;                            // [P]
+    constexpr BallRows<SIG> B;
+    TM *s_rs = (TM *)(s_att + P);                               // [B.base[w] + layer][P]
+    TM *s_eb = s_rs + (size_t)B.base[R + 1] * P;                // [2][P]
+    // neighbouring layers on one XCD, whose L2 then serves the overlap
+    const int lb = xcd_block((int)blockIdx.x, (int)gridDim.x);
+    const int z0 = lb / st.bands, y0 = (lb - z0 * st.bands) * st.ty;
+    const bool full = st.bands == 1;
+    const int nout = min(st.ty, L.ny - y0) * nx;   // nodes whose fields the block writes
+    const int o0 = full ? 0 : R * nx;              // the first of them in the block's P nodes
+    const int yb = full ? 0 : y0 - R;              // layer row of the block's row 0
+    const int lane = (int)threadIdx.x & 63, W = (int)blockDim.x >> 6;
+    const int wv = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int cpw = (P + 63) >> 6;                 // 64-node chunks of P, and of the output
+    const int cpo = (nout + 63) >> 6;
+    auto row_of = [&](int v) { return (int)__umulhi((uint32_t)v, st.magic); };
+    // layer l of the block is z0 - R + l
+    using Node = typename NodeOf<SRC>::type;
+    for (int it0 = wv; it0 < NL * cpw; it0 += Node::BATCH * W) {
+        Node nd[Node::BATCH];
+        int lq[Node::BATCH], rq[Node::BATCH];
+        bool in[Node::BATCH], fl[Node::BATCH], own[Node::BATCH];
+#pragma unroll
+        for (int k = 0; k < Node::BATCH; ++k) {
+            const int it = it0 + k * W, l = it / cpw, q = (it - l * cpw) * 64 + lane;
+            int z = z0 - R + l;
+            if (L.zper) {
+                while (z < 0) z += L.nz;
+                while (z >= L.nz) z -= L.nz;
+            }
+            in[k] = it < NL * cpw && q < P;
+            const int ly = row_of(q);
+            int y = yb + ly;
+            while (y < 0) y += L.ny;
+            while (y >= L.ny) y -= L.ny;
+            lq[k] = l * P + q;
+            rq[k] = q - ly * nx + nx * y;
+            own[k] = in[k] && l == R && q >= o0 && q < o0 + nout;
+            fl[k] = in[k] && z >= 0 && z < L.nz && is_fluid_z(L, z);
+            if (fl[k]) nd[k].load(L, src, z, rq[k], own[k]);
+        }
+#pragma unroll
+        for (int k = 0; k < Node::BATCH; ++k) {
+            if (!in[k]) continue;
+            double n = 0.0, j[3] = {0.0, 0.0, 0.0};
+            if (fl[k]) nd[k].moments(n, j);
+            s_rs[lq[k]] = (TM)n;
+            if (own[k]) {
+                if (ATT) store_padded(L, fld.n, rq[k], z0, (TM)n);
+                store_padded4(L, fld.nj, rq[k], z0, (TM)n, (TM)j[0], (TM)j[1], (TM)j[2]);
+            }
+        }
+    }
+    __syncthreads();
+    for (int it = wv; it < NL * cpw; it += W) {
+        const int l = it / cpw, q = (it - l * cpw) * 64 + lane;
+        if (q < P) {
+            const int x = q - row_of(q) * nx;
+            const TM *row = s_rs + l * P + (q - x);
+            TM acc = row[x];
+#pragma unroll
+            for (int w = 1; w <= R; ++w) {
+                acc += row[wrapr(x - w, nx)] + row[wrapr(x + w, nx)];
+                const int k = l - (R - B.reach[w]);  // its layer among those kept for w
+                if (k >= 0 && k < B.layers[w]) s_rs[(B.base[w] + k) * P + q] = acc;
+            }
+        }
+    }
+    if constexpr (ATT) {
+        for (int r = threadIdx.x; r < P; r += (int)blockDim.x) {
+            const int x = r - row_of(r) * nx;
+            const TM *row = s_rs + R * P + (r - x);
+            int xm = (x - aw.R) % nx;
+            xm = xm < 0 ? xm + nx : xm;
+            double s = 0.0;
+#pragma unroll 8
+            for (int m = 0; m <= 2 * aw.R; ++m) {
+                s += aw.w[m] * (double)row[xm];
+                xm = (xm + 1 == nx) ? 0 : xm + 1;
+            }
+            s_att[r] = s;
+        }
+    }
+    __syncthreads();
+    // eta_bar of layers z0 and z0 + 1 (the layer above a walled array: 0) at the
+    // output nodes and, in a band, the row after them
+    const int neb = full ? P : nout + nx, cpe = (neb + 63) >> 6;
+    for (int it = wv; it < 2 * cpe; it += W) {
+        const int k = it >= cpe ? 1 : 0, v = (it - k * cpe) * 64 + lane;
+        if (v < neb) {
+            const int q = o0 + v, y = row_of(q), x = q - y * nx;
+            double s = 0.0;
+            if (L.zper || z0 + k < L.nz) {
+#pragma unroll
+                for (int oy = -R; oy <= R; ++oy) {
+                    const TM *col = s_rs + x + nx * (full ? wrapr(y + oy, L.ny) : y + oy) + k * P;
+#pragma unroll
+                    for (int oz = -R; oz <= R; ++oz) {
+                        const int at = B.at[oy + R][oz + R];
+                        if (at >= 0) s += (double)col[at * P];
+                    }
+                }
+            }
+            s_eb[k * P + q] = (TM)(eta_pref * s);
+        }
+    }
+    if constexpr (ATT) {
+        for (int r = threadIdx.x; r < P; r += (int)blockDim.x) {
+            const int y = row_of(r), x = r - y * nx;
+            int ym = (y - aw.R) % L.ny;
+            ym = ym < 0 ? ym + L.ny : ym;
+            double s = 0.0;
+#pragma unroll 8
+            for (int m = 0; m <= 2 * aw.R; ++m) {
+                s += aw.w[m] * s_att[x + nx * ym];
+                ym = (ym + 1 == L.ny) ? 0 : ym + 1;
+            }
+            att_b[(size_t)L.plane * z0 + r] = s;
+        }
+    }
+    __syncthreads();
+    for (int it = wv; it < NGSLOT * cpo; it += W) {
+        const int b = it / cpo, v = (it - b * cpo) * 64 + lane;
+        if (v < nout) {
+            const int q = o0 + v, y = row_of(q), x = q - y * nx;
+            const int x1 = wrapc<1>(x, nx), y1 = full ? wrapc<1>(y, L.ny) : y + 1;
+            // the axes of the slot: a the first, o the second (x = 1, y = 2, z = 4)
+            const int a = b & -b, o = b ^ a;
+            auto e = [&](int m) -> double {
+                return (double)s_eb[((m & 1) ? x1 : x) + nx * ((m & 2) ? y1 : y) + ((m & 4) ? P : 0)];
+            };
+            const double ea = b == 0 ? e(0) : e(0) + e(a);
+            const double eta = b == 0 ? ea : (o == 0 ? 0.5 * ea : 0.25 * (ea + (e(o) + e(a | o))));
+            store_padded(L, fld.G + (size_t)b * L.fld_stride, q - o0 + nx * y0, z0, g2_t<TM>(eta, g2_model));
+        }
+    }
+    if constexpr (std::is_same<SRC, FieldSource>::value) {
+        if (threadIdx.x == 0 && y0 == 0) src.chi[z0] = wall_factor(L, SIG, src.wall_reg, z0);
+        if (!L.zper) {
+            // padding layers z0, z0 + nz, ... below and above the lattice
+            for (int p = z0; p < L.hz; p += L.nz) {
+                for (int k = 0; k < 2; ++k) {
+                    const size_t lay = (size_t)L.plane * (p + (k ? L.nz + L.hz : 0)) + (size_t)nx * y0;
+                    for (int q = threadIdx.x; q < 4 * nout; q += (int)blockDim.x) fld.nj[4 * lay + q] = (TM)0;
+                    for (int b = 0; b < NGSLOT; ++b)
+                        for (int q = threadIdx.x; q < nout; q += (int)blockDim.x) fld.G[(size_t)b * L.fld_stride + lay + q] = (TM)0;
+                }
+            }
+        }
+    }
+}
+
+// Part PART of the shell sum before its quadrature weight: 0..2 the axis pairs,
+// 3 + 2 plane + (0: point (1, 1), 1: point (1, -1)) the face diagonals.
+template <int SIG, int PART, typename TM, typename TC>
+__device__ __forceinline__ TC shell_part(const Fields<TM> &F, const LatticeDev &L, const NodeCtx<TC> &c, const TC *alpha)
+{
+    if constexpr (PART < 3) {
+        constexpr int X = PART == 0, Y = PART == 1, Z = PART == 2;
+        return pair_element<X * SIG, Y * SIG, Z * SIG, X, Y, Z, false, true>(F, L, c, c.u[PART]);
+    } else {
+        constexpr int PL = (PART - 3) / 2, SB = (PART - 3) % 2 ? -1 : 1;
+        const GlobalShell<true, TM> src{F, L};
+        return diag_pair_sum<PL, 1, SB, ell_of(SIG)>(src, c, alpha);
+    }
+}
+
+// phi at (x, y, z) from the attraction's x and y passes (k_att_z's sum).
+__device__ __forceinline__ double att_phi_z(const LatticeDev &L, const AttWeights &aw, const double *__restrict__ b,
+                                            int r, int z)
+{
+    double s = 0.0;
+    if (L.zper) {
+        int zm = (z - aw.R) % L.nz;
+        zm = zm < 0 ? zm + L.nz : zm;
+#pragma unroll 8
+        for (int m = 0; m <= 2 * aw.R; ++m) {
+            s += aw.w[m] * b[(size_t)L.plane * zm + r];
+            zm = (zm + 1 == L.nz) ? 0 : zm + 1;
+        }
+    } else {
+        const int m0 = max(0, aw.R - z), m1 = min(2 * aw.R, L.nz - 1 - z + aw.R);
+#pragma unroll 8
+        for (int m = m0; m <= m1; ++m) s += aw.w[m] * b[(size_t)L.plane * (z + m - aw.R) + r];
+    }
+    return -aw.eps * s;
+}
+
+// One direction's post-collision population as it is stored, and where (as
+// d_collide stores it).  The caller stores its directions together, after every
+// read of the reference table.
+template <typename TF>
+struct Streamed {
+    TF v;
+    TF *p;
+};
+template <int I, typename TF>
+__device__ __forceinline__ Streamed<TF> stream_one(const LatticeDev &L, const StepConst &sc, TF *__restrict__ fout, int x,
+                                                   int y, int z, uint32_t lk, double fp)
+{
+    const int xt = wrapr(x + CX[I], L.nx), yt = wrapr(y + CY[I], L.ny);
+    int zt = z + CZ[I], zl = zt;  // zl: a layer of the reference table
+    bool bounce = (lk >> I) & 1u;
+    if (L.zper) {
+        zt = (zt < 0) ? zt + L.nz : ((zt >= L.nz) ? zt - L.nz : zt);
+        zl = zt;
+    } else {
+        bounce = bounce || (zt < L.wall_lo) || (zt >= L.nz - L.wall_hi);
+        zl = (zt < 0 || zt >= L.nz) ? z : zt;
+    }
+    const double rb = layer_ref(sc.nref_w, z)[OPP[I]], rs = layer_ref(sc.nref_w, zl)[I];
+    Streamed<TF> o;
+    o.v = (TF)(fp - (bounce ? rb : rs));
+    o.p = fout + (bounce ? (size_t)OPP[I] * L.pop_stride + (x + L.nx * (y + L.ny * z))
+                         : (size_t)I * L.pop_stride + (xt + L.nx * (yt + L.ny * zt)));
+    return o;
+}
+
+// The step's collision, or (FORCE) the force alone into Fout, of 64 nodes of a
+// layer by six waves.  ATT: the attraction, from its x and y passes in att_b.
+// Every lane takes part in the barrier; lanes past the layer's end repeat its
+// last node and store nothing.
+template <int SIG, typename SRC, typename TF, typename TM, bool MASK, bool ATT, bool FORCE>
+__global__ __launch_bounds__(384) void k_collide_split(LatticeDev L, StepConst sc, const double *__restrict__ chi, SRC src,
+                                                       TF *__restrict__ fout, Fields<TM> fld, int cpp, AttWeights aw,
+                                                       const double *__restrict__ att_b, double *__restrict__ Fout)
+{
+    __shared__ double s_part[9][64], s_fa[3][64];
+    const int lane = (int)threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int lb = xcd_block((int)blockIdx.x, (int)gridDim.x);
+    const int zl = lb / cpp;
+    const int z = (FORCE || L.zper ? 0 : L.wall_lo) + zl;
+    const int rr = (lb - zl * cpp) * 64 + lane;
+    const bool act = rr < L.plane;
+    const int r = act ? rr : L.plane - 1;
+    const int y = r / L.nx, x = r - y * L.nx;
+    const int id = z * L.plane + r;
+    if (FORCE && !is_fluid_z(L, z)) {  // uniform over the block
+        if (act && w < 3) Fout[(size_t)w * L.N + id] = 0.0;
+        return;
+    }
+    uint32_t lk = 0;
+    if (MASK && sc.links) lk = sc.links[id];
+    // the populations of the wave's own directions
+    double fo[4];
+    if constexpr (!FORCE) {
+        const double *rf = layer_ref(src.nref, z);
+        auto own = [&](int k, int i) { fo[k] = (double)src.f[(size_t)i * L.pop_stride + id] + rf[i]; };
+        switch (w) {
+        case 0: own(0, 1), own(1, 2), own(2, 13), own(3, 14); break;
+        case 1: own(0, 3), own(1, 4), own(2, 15), own(3, 16); break;
+        case 2: own(0, 5), own(1, 6), own(2, 17), own(3, 18); break;
+        case 3: own(0, 7), own(1, 8); break;
+        case 4: own(0, 9), own(1, 10); break;
+        default: own(0, 11), own(1, 12), own(2, 0);
+        }
+    }
+    // n and j in FP64: FP64 fields hold just these sums, FP32 fields do not
+    double n, j[3];
+    if constexpr (sizeof(TM) == 8) {
+        double q[4];
+        load4(fld.nj + 4 * ((size_t)r + (size_t)L.plane * (z + L.hz)), q);
+        n = q[0], j[0] = q[1], j[1] = q[2], j[2] = q[3];
+    } else {
+        typename NodeOf<SRC>::type nd;
+        nd.load(L, src, z, r, true);
+        nd.moments(n, j);
+    }
+    const double inv_n = (n != 0.0) ? 1.0 / n : 0.0;
+    const double u[3] = {j[0] * inv_n, j[1] * inv_n, j[2] * inv_n};
+    if (sc.hs_on) {
+        NodeCtx<double> c;
+        c.x = x;
+        c.y = y;
+        c.zp = z + L.hz;
+        c.u[0] = u[0];
+        c.u[1] = u[1];
+        c.u[2] = u[2];
+        c.ckap = (MASK && sc.chi_n ? sc.chi_n[id] : chi[z]) * sc.kappa;
+        const double alpha[4] = {sc.alpha[0], sc.alpha[1], sc.alpha[2], sc.alpha[3]};
+#define HSLB_PART(W, P) s_part[P][lane] = shell_part<SIG, P>(fld, L, c, alpha)
+        switch (w) {
+        case 0: HSLB_PART(0, 3); break;
+        case 1: HSLB_PART(1, 4); HSLB_PART(1, 0); break;
+        case 2: HSLB_PART(2, 5); break;
+        case 3: HSLB_PART(3, 6); HSLB_PART(3, 1); break;
+        case 4: HSLB_PART(4, 7); break;
+        default: HSLB_PART(5, 8); HSLB_PART(5, 2); break;
+        }
+#undef HSLB_PART
+    }
+    if constexpr (ATT) {
+        if ((w & 1) == 0) {
+            const int a = w >> 1;
+            int rp = r, rm = r, zp = z, zm = z;
+            if (a == 0) {
+                rp = wrapc<1>(x, L.nx) + L.nx * y;
+                rm = wrapc<-1>(x, L.nx) + L.nx * y;
+            } else if (a == 1) {
+                rp = x + L.nx * wrapc<1>(y, L.ny);
+                rm = x + L.nx * wrapc<-1>(y, L.ny);
+            } else {
+                zp = z + 1;
+                zm = z - 1;
+                if (L.zper) {
+                    zp = (zp == L.nz) ? 0 : zp;
+                    zm = (zm < 0) ? L.nz - 1 : zm;
+                }
+            }
+            s_fa[a][lane] = -n * (att_phi_z(L, aw, att_b, rp, zp) - att_phi_z(L, aw, att_b, rm, zm)) / 2.0;
+        }
+    }
+    __syncthreads();
+    double Fv[3], S[3] = {0.0, 0.0, 0.0}, Fa[3] = {0.0, 0.0, 0.0};
+    if (sc.hs_on) {
+        double d[6];
+#pragma unroll
+        for (int k = 0; k < 6; ++k) d[k] = s_part[3 + k][lane];
+        // fused as the compiler fuses the sums of shell_sum
+        constexpr double K = (1.0 / 15.0) * 0.70710678118654752440, K1 = 1.0 / 30.0;
+        const double w0 = K * d[0], w2 = K * d[2];
+        S[0] = fma(K1, s_part[0][lane], w0), S[1] = fma(K1, s_part[1][lane], w0);
+        S[2] = fma(K1, s_part[2][lane], w2);
+        S[0] = fma(K, d[1], S[0]), S[1] = fma(-K, d[1], S[1]);
+        S[0] = fma(K, d[2], S[0]);
+        S[0] = fma(K, d[3], S[0]), S[2] = fma(-K, d[3], S[2]);
+        S[1] = fma(K, d[4], S[1]), S[2] = fma(K, d[4], S[2]);
+        S[1] = fma(K, d[5], S[1]), S[2] = fma(-K, d[5], S[2]);
+    }
+    if constexpr (ATT) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) Fa[a] = s_fa[a][lane];
+    }
+    const double pn = sc.pref * n;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) Fv[a] = fma(n, sc.g[a], fma(pn, S[a], Fa[a]));
+    if constexpr (FORCE) {
+        if (act && w < 3) Fout[(size_t)w * L.N + id] = w == 0 ? Fv[0] : (w == 1 ? Fv[1] : Fv[2]);
+    } else {
+        if (!act) return;
+        if (MASK && (lk & LINK_SOLID)) {
+            // a solid node restates its zero populations
+            if (w == 0) {
+                const double *rw = layer_ref(sc.nref_w, z);
+#pragma unroll
+                for (int i = 0; i < NQ; ++i) fout[(size_t)i * L.pop_stride + id] = (TF)(0.0 - rw[i]);
+            }
+            return;
+        }
+        const double uu = u[0] * u[0] + u[1] * u[1] + u[2] * u[2];
+        const double omega = 1.0 / sc.tau;
+        const double base = 1.0 - 1.5 * uu;
+        Streamed<TF> o[4];
+        auto pair = [&](auto ic, int k) {
+            // fused where the general kernel's code is (its plus direction), so
+            // that both round alike
+#pragma clang fp contract(off)
+            constexpr int i = decltype(ic)::value;
+            const double f0 = fo[k], f1 = fo[k + 1];
+            const double cu = CX[i] * u[0] + CY[i] * u[1] + CZ[i] * u[2];
+            const double cF = CX[i] * Fv[0] + CY[i] * Fv[1] + CZ[i] * Fv[2];
+            const double wn = wq(i) * n, wn3 = 3.0 * wn;
+            const double A = wn * fma(4.5 * cu, cu, base);
+            const double B = wn3 * cu, sr = (3.0 * wq(i)) * cF;
+            o[k] = stream_one<i>(L, sc, fout, x, y, z, lk, fma(-omega, f0 - fma(wn3, cu, A), fma(3.0 * wq(i), cF, f0)));
+            o[k + 1] = stream_one<i + 1>(L, sc, fout, x, y, z, lk, fma(-omega, f1 - (A - B), f1 - sr));
+        };
+        auto store = [&](int cnt) {
+#pragma unroll
+            for (int k = 0; k < cnt; ++k) *o[k].p = o[k].v;
+        };
+        using std::integral_constant;
+        switch (w) {
+        case 0:
+            pair(integral_constant<int, 1>{}, 0);
+            pair(integral_constant<int, 13>{}, 2);
+            store(4);
+            break;
+        case 1:
+            pair(integral_constant<int, 3>{}, 0);
+            pair(integral_constant<int, 15>{}, 2);
+            store(4);
+            break;
+        case 2:
+            pair(integral_constant<int, 5>{}, 0);
+            pair(integral_constant<int, 17>{}, 2);
+            store(4);
+            break;
+        case 3:
+            pair(integral_constant<int, 7>{}, 0);
+            store(2);
+            break;
+        case 4:
+            pair(integral_constant<int, 9>{}, 0);
+            store(2);
+            break;
+        default: {
+            pair(integral_constant<int, 11>{}, 0);
+            const double f0 = fo[2];
+            o[2] = stream_one<0>(L, sc, fout, x, y, z, lk, f0 - omega * (f0 - (1.0 / 3.0) * n * base));
+            store(3);
+        }
+        }
+    }
 }
 
 // ------------------------------------------------- mean-field attraction
@@ -2612,6 +3200,194 @@ hipError_t launch_attraction(hipStream_t s, const LatticeDev &L, const AttWeight
     return hipGetLastError();
 }
 
+// Which lattices take the small-lattice kernels (us per step, MI355X; general
+// kernels / split collide / both):
+//   8x8x24 sigma 4 FP64    17.0 / 13.6 / 10.3    16x16x26 sigma 8 FP32   18.3 / 14.2 / 15.3
+//   9x9x73 sigma 7 FP32    18.8 / 15.6 / 13.0    24x20x30 sigma 8 FP64   24.1 / 17.6 / 24.0
+//   16x16x40 sigma 4 FP64  20.0 / 13.6 / 12.5    16x16x128 sigma 8 FP32  18.9 / 16.2 / 18.8
+//   16x16x128 sigma 4 FP64 23.3 / 18.5 / 17.2    32x32x32 sigma 4 FP32   18.0 / 15.3 / 16.8
+//   16x16x256 sigma 8 FP64 30.5 / 29.5 / 29.7    16x16x256 sigma 8 FP32  21.5 / 22.1 / 22.4
+//   32x32x64 sigma 6 FP64  27.0 / 25.9 / 34.7    64x64x40 sigma 8 FP64   40.6 / 43.7 / 43.7
+// The split collide wins until its six waves per 64 nodes fill the chip (64 Ki
+// nodes with FP64 fields, which hold the moments; 40 Ki with FP32, where each
+// wave sums the populations again).  The fields kernel wins while a block forms
+// the densities of at most 1536 nodes (one and a half per lane): beyond, the
+// layers it repeats cost more than the launches it saves.
+constexpr int kSplitNodes64 = 65536, kSplitNodes32 = 40960, kFieldsNodes = 32768, kFieldsBlock = 1536;
+constexpr int kSmallBlocks = 256;
+constexpr size_t kSmallLds = 156 * 1024;
+
+// Bands per layer: as many as bring the grid to kSmallBlocks blocks while a band
+// keeps at least two rows and is narrower than the layer with its halo; more
+// where the LDS asks for it.  one: a single band (the blocks that read
+// populations, whose halo costs 19 loads a node).
+bool small_tile(const LatticeDev &L, int sigma, size_t tm, bool one, SmallTile &t)
+{
+    const int R = sigma / 2, halo = 2 * R + 1;
+    t.magic = (uint32_t)((((uint64_t)1 << 32) + L.nx - 1) / (uint64_t)L.nx);
+    t.bands = 1;
+    t.ty = t.rows = L.ny;
+    bool fits = fields_small_lds(sigma, L.plane, tm) <= kSmallLds && L.plane < 65536;
+    if (one) return fits;
+    const int want = std::max(1, kSmallBlocks / std::max(1, L.nz));
+    for (int b = 2; L.ny / b >= 2; ++b) {
+        if (fits && b > want) break;
+        const int ty = (L.ny + b - 1) / b, rows = ty + halo;
+        if (rows >= L.ny) {
+            if (fits) continue;
+        }
+        if (fields_small_lds(sigma, rows * L.nx, tm) > kSmallLds || rows * L.nx >= 65536) continue;
+        t.ty = ty;
+        t.bands = (L.ny + ty - 1) / ty;
+        t.rows = rows;
+        fits = true;
+    }
+    return fits;
+}
+
+bool fields_small_apply(const LatticeDev &L, int sigma, size_t tm)
+{
+    SmallTile t;
+    return sigma >= 2 && sigma <= 8 && L.N <= kFieldsNodes && (2 * (sigma / 2) + 2) * L.plane <= kFieldsBlock &&
+           small_tile(L, sigma, tm, true, t);
+}
+
+bool force_fields_apply(const LatticeDev &L, int sigma)
+{
+    SmallTile t;
+    return sigma >= 2 && sigma <= 8 && L.N <= kSplitNodes64 && small_tile(L, sigma, sizeof(double), false, t);
+}
+
+// Lattices that the LDS-staged collide takes keep the choice between it and the
+// direct kernel.
+bool collide_split_apply(const LatticeDev &L, int sigma, const StepConst &c, size_t tm)
+{
+    return sigma >= 2 && sigma <= 8 && c.hs_on && L.N <= (tm == 8 ? kSplitNodes64 : kSplitNodes32) &&
+           !collide_tiles_apply(L, sigma, c, tm == 4);
+}
+
+template <int SIG, typename SRC, typename TM, bool ATT>
+hipError_t launch_fields_small_t(hipStream_t s, const LatticeDev &L, double eta_pref, int g2_model, SRC src,
+                                 Fields<TM> fld, const AttWeights &aw, double *att_b)
+{
+    SmallTile t;
+    if (!small_tile(L, SIG, sizeof(TM), !std::is_same<SRC, FieldSource>::value, t)) return hipErrorInvalidValue;
+    const int nodes = t.rows * L.nx;
+    const size_t lds = fields_small_lds(SIG, nodes, sizeof(TM));
+    auto kern = k_fields_small<SIG, SRC, TM, ATT>;
+    if (lds > 64 * 1024) {
+        const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    const int waves = std::min(16, (2 * (SIG / 2) + 2) * ((nodes + 63) / 64));
+    hipLaunchKernelGGL(kern, dim3((unsigned)(L.nz * t.bands)), dim3((unsigned)(64 * waves)), lds, s, L, src, fld, eta_pref,
+                       g2_model, t, aw, att_b);
+    return hipGetLastError();
+}
+
+template <typename SRC, typename TM>
+hipError_t launch_fields_small_src(hipStream_t s, const LatticeDev &L, int sigma, double eta_pref, int g2_model, SRC src,
+                                   Fields<TM> fld, const AttWeights *aw, double *att_b)
+{
+#define HSLB_FS(SG)                                                                                            \
+    case SG:                                                                                                   \
+        if constexpr (!std::is_same<SRC, FieldSource>::value)                                                  \
+            if (aw) return launch_fields_small_t<SG, SRC, TM, true>(s, L, eta_pref, g2_model, src, fld, *aw, att_b); \
+        return launch_fields_small_t<SG, SRC, TM, false>(s, L, eta_pref, g2_model, src, fld, AttWeights{}, nullptr);
+    switch (sigma) {
+        HSLB_FS(2)
+        HSLB_FS(3)
+        HSLB_FS(4)
+        HSLB_FS(5)
+        HSLB_FS(6)
+        HSLB_FS(7)
+        HSLB_FS(8)
+    default: return hipErrorInvalidValue;
+    }
+#undef HSLB_FS
+}
+
+template <typename TF, typename TM>
+hipError_t launch_fields_small(hipStream_t s, const LatticeDev &L, int sigma, double eta_pref, int g2_model,
+                               const double *nref, const TF *f, Fields<TM> fld, const AttWeights *aw, double *att_b)
+{
+    if (!fields_small_apply(L, sigma, sizeof(TM))) return hipErrorInvalidValue;
+    return launch_fields_small_src(s, L, sigma, eta_pref, g2_model, PopSource<TF>{f, nref}, fld, aw, att_b);
+}
+
+template <int SIG, typename SRC, typename TF, typename TM, bool FORCE>
+hipError_t launch_collide_split_t(hipStream_t s, const LatticeDev &L, const StepConst &c, const double *chi, SRC src,
+                                  TF *fout, Fields<TM> fld, const AttWeights *aw, const double *att_b, double *F)
+{
+    const int layers = FORCE || L.zper ? L.nz : L.nz - L.wall_lo - L.wall_hi;
+    const int cpp = (L.plane + 63) / 64;
+    const dim3 g((unsigned)(cpp * layers)), b(384);
+    const bool mask = c.links != nullptr;
+    if constexpr (FORCE) {
+        hipLaunchKernelGGL((k_collide_split<SIG, SRC, TF, TM, false, false, true>), g, b, 0, s, L, c, chi, src, fout, fld,
+                           cpp, AttWeights{}, nullptr, F);
+    } else if (mask && aw) {
+        hipLaunchKernelGGL((k_collide_split<SIG, SRC, TF, TM, true, true, false>), g, b, 0, s, L, c, chi, src, fout, fld,
+                           cpp, *aw, att_b, F);
+    } else if (mask) {
+        hipLaunchKernelGGL((k_collide_split<SIG, SRC, TF, TM, true, false, false>), g, b, 0, s, L, c, chi, src, fout, fld,
+                           cpp, AttWeights{}, nullptr, F);
+    } else if (aw) {
+        hipLaunchKernelGGL((k_collide_split<SIG, SRC, TF, TM, false, true, false>), g, b, 0, s, L, c, chi, src, fout, fld,
+                           cpp, *aw, att_b, F);
+    } else {
+        hipLaunchKernelGGL((k_collide_split<SIG, SRC, TF, TM, false, false, false>), g, b, 0, s, L, c, chi, src, fout, fld,
+                           cpp, AttWeights{}, nullptr, F);
+    }
+    return hipGetLastError();
+}
+
+template <typename TF, typename TM>
+hipError_t launch_collide_split(hipStream_t s, const LatticeDev &L, int sigma, const StepConst &c, const double *chi,
+                                const TF *fin, TF *fout, Fields<TM> fld, const AttWeights *aw, const double *att_b)
+{
+    if (!collide_split_apply(L, sigma, c, sizeof(TM))) return hipErrorInvalidValue;
+    using S = PopSource<TF>;
+    const S src{fin, c.nref_r};
+#define HSLB_CS(SG) \
+    case SG: return launch_collide_split_t<SG, S, TF, TM, false>(s, L, c, chi, src, fout, fld, aw, att_b, nullptr);
+    switch (sigma) {
+        HSLB_CS(2)
+        HSLB_CS(3)
+        HSLB_CS(4)
+        HSLB_CS(5)
+        HSLB_CS(6)
+        HSLB_CS(7)
+        HSLB_CS(8)
+    default: return hipErrorInvalidValue;
+    }
+#undef HSLB_CS
+}
+
+hipError_t launch_force_fields(hipStream_t s, const LatticeDev &L, int sigma, int wall_reg, const StepConst &c, double *chi,
+                               const double *n, const double *u, Fields<double> fld, double *F)
+{
+    if (!force_fields_apply(L, sigma)) return hipErrorInvalidValue;
+    using S = FieldSource;
+    const S src{n, u, chi, wall_reg};
+    hipError_t e = launch_fields_small_src(s, L, sigma, c.eta_pref, c.g2_model, src, fld, (const AttWeights *)nullptr,
+                                           (double *)nullptr);
+    if (e != hipSuccess) return e;
+#define HSLB_FF(SG) \
+    case SG: return launch_collide_split_t<SG, S, double, double, true>(s, L, c, chi, src, nullptr, fld, nullptr, nullptr, F);
+    switch (sigma) {
+        HSLB_FF(2)
+        HSLB_FF(3)
+        HSLB_FF(4)
+        HSLB_FF(5)
+        HSLB_FF(6)
+        HSLB_FF(7)
+        HSLB_FF(8)
+    default: return hipErrorInvalidValue;
+    }
+#undef HSLB_FF
+}
+
 hipError_t launch_round_f32(hipStream_t s, double *a, int count)
 {
     hipLaunchKernelGGL(k_round_f32, dim3(blocks_for(count)), dim3(256), 0, s, a, count);
@@ -3071,6 +3847,12 @@ hipError_t launch_batch_profiles(hipStream_t s, const SlitDesc *desc, const Work
                                                Fields<TM>);                                                 \
     template hipError_t launch_moments_rs<TF, TM>(hipStream_t, const LatticeDev &, int, const double *,      \
                                                   const TF *, Fields<TM>, TM *, bool);                      \
+    template hipError_t launch_fields_small<TF, TM>(hipStream_t, const LatticeDev &, int, double, int,         \
+                                                    const double *, const TF *, Fields<TM>, const AttWeights *, \
+                                                    double *);                                                  \
+    template hipError_t launch_collide_split<TF, TM>(hipStream_t, const LatticeDev &, int, const StepConst &,   \
+                                                     const double *, const TF *, TF *, Fields<TM>,              \
+                                                     const AttWeights *, const double *);                       \
     template hipError_t launch_collide<TF, TM>(hipStream_t, const LatticeDev &, int, const StepConst &,    \
                                                const double *, const TF *, TF *, Fields<TM>, bool);         \
     template hipError_t launch_force<TF, TM>(hipStream_t, const LatticeDev &, int, const StepConst &,      \
@@ -3098,13 +3880,7 @@ __global__ __launch_bounds__(256) void k_fill(double *__restrict__ a, size_t cou
 __global__ __launch_bounds__(256) void k_chi(LatticeDev L, int sigma, int wall_reg, double *__restrict__ chi)
 {
     const int z = blockIdx.x * 256 + threadIdx.x;
-    if (z >= L.nz) return;
-    double c = 1.0;
-    if (!L.zper && wall_reg) {
-        const double za = L.wall_lo - 0.5, zb = L.nz - L.wall_hi - 0.5;
-        c = 1.0 - exp(-fmin((double)z - za, zb - (double)z) / (double)sigma);
-    }
-    chi[z] = c;
+    if (z < L.nz) chi[z] = wall_factor(L, sigma, wall_reg, z);
 }
 
 }  // namespace
