@@ -678,91 +678,165 @@ __host__ __device__ inline RowSplit row_split(const Geo &g, int max_chunks)
     return r;
 }
 
-constexpr int WG_CHUNKS_CH = 64;    // layers 2, 3: waves = 25 tap rows x chunks
 constexpr int WG_CHUNKS_TAP = 1024; // layer 1: waves = chunks
 
 // Layers 2 and 3: M = input channel (2 x 16), N = output channel (NB x 16),
-// K = nodes.  Wave = (tap row (dz, dy), chunk of lattice rows); the 5 dx taps
-// share the three chunks loaded per channel.
-// partial[wave][5][32][16 NB]
-template <int NB>
-__global__ __launch_bounds__(256) void k_wgrad_ch(Geo g, RowSplit rs, int cout, const uint16_t *__restrict__ actT,
-                                                  const uint16_t *__restrict__ gT, float *__restrict__ partial)
+// K = nodes.  A block takes one dz and a run of lattice rows (a chunk), ten
+// waves: wave (dy, mi) the five dx taps of one dy and 16 input channels.  The
+// block marches along y, two rows a step: the input rows y - 2 .. y + 3 of
+// z + dz lie in a ring of eight LDS rows (with 8 nodes of x halo on either
+// side, periodic), so that each is loaded once for the 25 taps, and the two
+// rows of the output gradient in a double buffer; the next step's rows are
+// loaded during the products and written behind them, one barrier a step.  A
+// lane reads its 8 nodes and the two next to them once and forms the five
+// shifted operands by funnel shifts.  The rows' LDS strides are odd multiples
+// of 16 bytes (no bank conflicts among the 16 channels of a read).
+//   What bounds it: 64 x 64 x 88, layer 2 (92 GFLOP): the earlier kernel (a
+// wave per (dz, dy), operands straight from L2, 2.3 GB of it) took 349 us;
+// staged, the reads are 0.23 GB.
+// partial[chunk][dz][dy][dx][32][16 NB]
+constexpr int WG_CHUNKS = 102;  // x 5 dz: two blocks per compute unit
+constexpr int WG_WAVES = 10, WG_RING = 8;
+
+// x tile of a row: 64 nodes where they divide it, else 32
+__host__ __device__ inline int wg_xt(const Geo &g) { return g.nx % 64 == 0 ? 64 : 32; }
+// row pairs a block of offset dz has to share with the others, and its first z
+__host__ __device__ inline int wg_pairs(const Geo &g, int dz, int &z0)
 {
-    const int lane = threadIdx.x & 63;
-    const int wave = blockIdx.x * 4 + (int)(threadIdx.x >> 6);
-    if (wave >= 25 * rs.chunks) return;
-    const int gq = wave % 25, chunk = wave / 25;
-    const int dz = gq / 5 - 2, dy = gq % 5 - 2;
+    const int a = dz < 0 ? -dz : dz;
+    z0 = g.zper || dz > 0 ? 0 : a;
+    const int zs = g.zper ? g.nz : (g.nz > a ? g.nz - a : 0);
+    return (g.nx / wg_xt(g)) * zs * (g.ny / 2);
+}
+
+template <int NB, int XT>
+__global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks, int cout, const uint16_t *__restrict__ actT,
+                                                              const uint16_t *__restrict__ gT, float *__restrict__ partial)
+{
+    constexpr int SA = XT + 24, SB = XT + 8;       // row strides in elements
+    constexpr int CA = XT / 8 + 2, CB = XT / 8;    // 16-byte chunks of a row
+    constexpr int T = 64 * WG_WAVES;
+    __shared__ __attribute__((aligned(16))) uint16_t s_a[WG_RING][32][SA];
+    __shared__ __attribute__((aligned(16))) uint16_t s_b[2][2][16 * NB][SB];
+    const int dz = (int)blockIdx.x / chunks - 2, chunk = (int)blockIdx.x % chunks;
+    const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int li = lane & 15, lg = lane >> 4;
-    f32x4 acc[5][2][NB];
+    const int dy = w % 5 - 2, mi = w / 5;
+    f32x4 acc[5][NB];
 #pragma unroll
     for (int d = 0; d < 5; ++d)
 #pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[d][mi][nb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int nb = 0; nb < NB; ++nb) acc[d][nb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    if constexpr (NB == 1) {
+        // channels past cout stay zero
+        for (int q = threadIdx.x; q < 2 * 2 * 16 * NB * SB / 8; q += T) ((u32x4 *)s_b)[q] = (u32x4){0u, 0u, 0u, 0u};
+    }
 
-    const int r0 = chunk * rs.rpw, r1 = min(rs.rows, r0 + rs.rpw);
-    for (int row = r0; row < r1; ++row) {
-        const int y = row % g.ny, z = row / g.ny;
-        const int zs = zsrc(g, z + dz);
-        if (zs < 0) continue;  // the tap reads beyond the walls: zero
-        const size_t srow = (size_t)g.nx * (wrapi(y + dy, g.ny) + g.ny * zs);
-        const size_t orow = (size_t)g.nx * (y + g.ny * z);
-        for (int x0 = 0; x0 < g.nx; x0 += 32) {
-            const int xc = x0 + 8 * lg;
-            bf16x8 bv[NB];
+    int zfirst;
+    const int pairs = wg_pairs(g, dz, zfirst), ph = g.ny / 2, zcount = g.zper ? g.nz : (g.nz > abs(dz) ? g.nz - abs(dz) : 0);
+    const int p0 = (int)((int64_t)pairs * chunk / chunks), p1 = (int)((int64_t)pairs * (chunk + 1) / chunks);
+    // pair p: segment p / (zcount ph), layer, rows 2 (p % ph) and the next
+    auto place = [&](int p, int &x0, int &z, int &y) {
+        const int col = p / ph;
+        y = 2 * (p - col * ph);
+        const int seg = col / zcount;
+        x0 = seg * XT;
+        z = zfirst + col - seg * zcount;
+    };
+    // 16-byte chunk k of the two input rows (Y, Y + 1) / output-gradient rows
+    auto load_a = [&](int k, int x0, int zs, int Y) -> u32x4 {
+        const int c = k % CA, ch = (k / CA) & 31, row = k / (CA * 32);
+        const int x = wrapi(x0 - 8 + 8 * c, g.nx);
+        return *(const u32x4 *)(actT + (size_t)ch * g.N + x + (size_t)g.nx * (mod_pos(Y + row, g.ny) + (size_t)g.ny * zs));
+    };
+    auto put_a = [&](int k, int Y, u32x4 v) {
+        const int c = k % CA, ch = (k / CA) & 31, row = k / (CA * 32);
+        *(u32x4 *)&s_a[(Y + row) & (WG_RING - 1)][ch][8 * c] = v;
+    };
+    auto load_b = [&](int k, int x0, int z, int y) -> u32x4 {
+        const int c = k % CB, ch = (k / CB) % cout, row = k / (CB * cout);
+        return *(const u32x4 *)(gT + (size_t)ch * g.N + x0 + 8 * c + (size_t)g.nx * (y + row + (size_t)g.ny * z));
+    };
+    auto put_b = [&](int k, int buf, u32x4 v) {
+        const int c = k % CB, ch = (k / CB) % cout, row = k / (CB * cout);
+        *(u32x4 *)&s_b[buf][row][ch][8 * c] = v;
+    };
+    constexpr int NA = 2 * 32 * CA;                 // chunks of two input rows: at most one per thread
+    static_assert(NA <= T && 2 * 16 * NB * CB <= T, "one chunk per thread and step");
+    const int nbk = 2 * cout * CB;
+    const int t = threadIdx.x;
+    bool fresh = true;
+    int buf = 0;
+    for (int p = p0; p < p1; ++p) {
+        int x0, z, y;
+        place(p, x0, z, y);
+        const int zs = g.zper ? mod_pos(z + dz, g.nz) : z + dz;
+        if (fresh) {
+            // the first pair of a run: rows y - 2 .. y + 3 and the pair itself
+            __syncthreads();  // every wave is done with the ring
+            for (int r = 0; r < 3; ++r)
+                if (t < NA) put_a(t, y - 2 + 2 * r, load_a(t, x0, zs, y - 2 + 2 * r));
+            if (t < nbk) put_b(t, buf, load_b(t, x0, z, y));
+            __syncthreads();
+        }
+        // the next pair continues the run unless the layer (or the chunk) ends
+        const bool more = y + 2 < g.ny && p + 1 < p1;
+        u32x4 na = {0u, 0u, 0u, 0u}, nb_ = {0u, 0u, 0u, 0u};
+        if (more) {
+            if (t < NA) na = load_a(t, x0, zs, y + 4);
+            if (t < nbk) nb_ = load_b(t, x0, z, y + 2);
+        }
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb) {
-                const int co = 16 * nb + li;
-                u32x4 w = {0u, 0u, 0u, 0u};
-                if (co < cout) w = *(const u32x4 *)(gT + (size_t)co * g.N + orow + xc);
-                bv[nb] = as_bf(w);
-            }
-            const int xp = xc == 0 ? g.nx - 8 : xc - 8, xn = xc + 8 == g.nx ? 0 : xc + 8;
+        for (int row = 0; row < 2; ++row) {
+            const uint16_t *ra = &s_a[(y + row + dy) & (WG_RING - 1)][16 * mi + li][8];
 #pragma unroll
-            for (int mi = 0; mi < 2; ++mi) {
-                const uint16_t *base = actT + (size_t)(16 * mi + li) * g.N + srow;
-                const u32x4 prv = *(const u32x4 *)(base + xp);
-                const u32x4 cur = *(const u32x4 *)(base + xc);
-                const u32x4 nxt = *(const u32x4 *)(base + xn);
+            for (int k = 0; k < XT / 32; ++k) {
+                const int x = 32 * k + 8 * lg;
+                bf16x8 bv[NB];
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) bv[nb] = as_bf(*(const u32x4 *)&s_b[buf][row][16 * nb + li][x]);
+                const u32x4 cur = *(const u32x4 *)(ra + x);
+                u32x4 prv, nxt;
+                prv[3] = *(const uint32_t *)(ra + x - 2);
+                nxt[0] = *(const uint32_t *)(ra + x + 8);
 #pragma unroll
                 for (int d = 0; d < 5; ++d) {
                     const bf16x8 av = as_bf(shifted(prv, cur, nxt, d - 2));
 #pragma unroll
                     for (int nb = 0; nb < NB; ++nb)
-                        acc[d][mi][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv[nb], acc[d][mi][nb], 0, 0, 0);
+                        acc[d][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv[nb], acc[d][nb], 0, 0, 0);
                 }
             }
         }
+        if (more) {
+            if (t < NA) put_a(t, y + 4, na);
+            if (t < nbk) put_b(t, buf ^ 1, nb_);
+            __syncthreads();
+            buf ^= 1;
+        }
+        fresh = !more;
     }
-    float *out = partial + (size_t)wave * 5 * 32 * 16 * NB;
+    float *out = partial + ((size_t)(chunk * 5 + dz + 2) * 25 + (size_t)(dy + 2) * 5) * 32 * 16 * NB;
 #pragma unroll
     for (int d = 0; d < 5; ++d)
 #pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
+        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int ci = 16 * mi + 4 * lg + j, co = 16 * nb + li;
-                    out[((size_t)d * 32 + ci) * 16 * NB + co] = acc[d][mi][nb][j];
-                }
+            for (int j = 0; j < 4; ++j)
+                out[((size_t)d * 32 + 16 * mi + 4 * lg + j) * 16 * NB + 16 * nb + li] = acc[d][nb][j];
 }
 
-// dW[co][ci][t] = sum over chunks, t = gq * 5 + d; threads run over co
-// fastest, then ci, so that neighbouring threads read neighbouring partials
+// dW[co][ci][t] = sum over chunks; threads run over co fastest, then ci, so
+// that neighbouring threads read neighbouring partials
 __global__ __launch_bounds__(256) void k_wgrad_ch_reduce(int chunks, int nb16, int cout, const float *__restrict__ partial,
                                                          float *__restrict__ dW)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= cout * 32 * NT) return;
     const int co = i % cout, ci = (i / cout) % 32, t = i / (cout * 32);
-    const int gq = t / 5, d = t % 5;
     double s = 0.0;
-    for (int c = 0; c < chunks; ++c)
-        s += partial[(((size_t)(c * 25 + gq) * 5 + d) * 32 + ci) * nb16 + co];
+#pragma unroll 8
+    for (int c = 0; c < chunks; ++c) s += partial[(((size_t)c * NT + t) * 32 + ci) * nb16 + co];
     dW[(co * 32 + ci) * NT + t] = (float)s;
 }
 
@@ -822,16 +896,24 @@ __global__ __launch_bounds__(256) void k_wgrad_tap(Geo g, RowSplit rs, const uin
             for (int j = 0; j < 4; ++j) out[(16 * mi + 4 * lg + j) * 32 + 16 * nb + li] = acc[mi][nb][j];
 }
 
-// dW1[co][0][t]; threads run over co fastest (neighbouring partials)
+// dW1[co][0][t]: a block per tap, 8 groups of 32 threads (co) over the chunks,
+// the groups' sums added in order (a thread per (co, t) walking all 1024 chunks
+// left 240 of the 256 compute units idle and took 219 us)
 __global__ __launch_bounds__(256) void k_wgrad_tap_reduce(int chunks, const float *__restrict__ partial,
                                                           float *__restrict__ dW)
 {
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= 32 * NT) return;
-    const int co = i % 32, t = i / 32;
+    __shared__ double s_sum[8][32];
+    const int co = threadIdx.x & 31, grp = threadIdx.x >> 5, t = blockIdx.x;
     double s = 0.0;
-    for (int c = 0; c < chunks; ++c) s += partial[((size_t)c * 128 + t) * 32 + co];
-    dW[co * NT + t] = (float)s;
+#pragma unroll 8
+    for (int c = grp; c < chunks; c += 8) s += partial[((size_t)c * 128 + t) * 32 + co];
+    s_sum[grp][co] = s;
+    __syncthreads();
+    if (grp == 0) {
+#pragma unroll
+        for (int k = 1; k < 8; ++k) s += s_sum[k][co];
+        dW[co * NT + t] = (float)s;
+    }
 }
 
 // --------------------------------------------------------- reductions
@@ -1075,8 +1157,17 @@ hipError_t launch_conv_fwd(hipStream_t s, int cin, int cout, int epi, const FwdA
 size_t wgrad_partial_floats(const Geo &g, int layer)
 {
     if (layer == 1) return (size_t)row_split(g, WG_CHUNKS_TAP).chunks * 128 * 32;
-    const int nb = layer == 2 ? 2 : 1;
-    return (size_t)25 * row_split(g, WG_CHUNKS_CH).chunks * 5 * 32 * 16 * nb;
+    return (size_t)WG_CHUNKS * NT * 32 * 16 * (layer == 2 ? 2 : 1);
+}
+
+template <int NB>
+void launch_wgrad_rows(hipStream_t s, const Geo &g, int cout, const uint16_t *src, const uint16_t *gT, float *partial)
+{
+    const dim3 grid(5 * WG_CHUNKS), blk(64 * WG_WAVES);
+    if (wg_xt(g) == 64)
+        hipLaunchKernelGGL((k_wgrad_rows<NB, 64>), grid, blk, 0, s, g, WG_CHUNKS, cout, src, gT, partial);
+    else
+        hipLaunchKernelGGL((k_wgrad_rows<NB, 32>), grid, blk, 0, s, g, WG_CHUNKS, cout, src, gT, partial);
 }
 
 hipError_t launch_wgrad(hipStream_t s, int layer, const Geo &g, const uint16_t *src, const uint16_t *gT,
@@ -1085,17 +1176,15 @@ hipError_t launch_wgrad(hipStream_t s, int layer, const Geo &g, const uint16_t *
     if (layer == 1) {
         const RowSplit rs = row_split(g, WG_CHUNKS_TAP);
         hipLaunchKernelGGL(k_wgrad_tap, dim3((rs.chunks + 3) / 4), dim3(256), 0, s, g, rs, src, gT, partial);
-        hipLaunchKernelGGL(k_wgrad_tap_reduce, dim3(nblocks(32 * NT)), dim3(256), 0, s, rs.chunks, partial, dW);
+        hipLaunchKernelGGL(k_wgrad_tap_reduce, dim3(NT), dim3(256), 0, s, rs.chunks, partial, dW);
         return hipGetLastError();
     }
-    const RowSplit rs = row_split(g, WG_CHUNKS_CH);
-    const unsigned grid = (unsigned)((25 * rs.chunks + 3) / 4);
     if (layer == 2) {
-        hipLaunchKernelGGL(k_wgrad_ch<2>, dim3(grid), dim3(256), 0, s, g, rs, CH, src, gT, partial);
-        hipLaunchKernelGGL(k_wgrad_ch_reduce, dim3(nblocks(CH * 32 * NT)), dim3(256), 0, s, rs.chunks, 32, CH, partial, dW);
+        launch_wgrad_rows<2>(s, g, CH, src, gT, partial);
+        hipLaunchKernelGGL(k_wgrad_ch_reduce, dim3(nblocks(CH * 32 * NT)), dim3(256), 0, s, WG_CHUNKS, 32, CH, partial, dW);
     } else {
-        hipLaunchKernelGGL(k_wgrad_ch<1>, dim3(grid), dim3(256), 0, s, g, rs, CO, src, gT, partial);
-        hipLaunchKernelGGL(k_wgrad_ch_reduce, dim3(nblocks(CO * 32 * NT)), dim3(256), 0, s, rs.chunks, 16, CO, partial, dW);
+        launch_wgrad_rows<1>(s, g, CO, src, gT, partial);
+        hipLaunchKernelGGL(k_wgrad_ch_reduce, dim3(nblocks(CO * 32 * NT)), dim3(256), 0, s, WG_CHUNKS, 16, CO, partial, dW);
     }
     return hipGetLastError();
 }
