@@ -116,12 +116,27 @@ __device__ __forceinline__ uint32_t gelu_bf16(float z)
     return f2bf(v);
 }
 
-// bf16(d GELU'(z)), GELU'(z) = Phi(z) + z phi(z), in the reference form: the
-// two terms cancel near z = -0.75, where the fast form's error would grow
-// past the tie window (the input gradient is a training kernel).
+// d GELU'(z), GELU'(z) = Phi(z) + z phi(z), in the reference form, out of line.
+__device__ __attribute__((noinline)) float dgelu_ref(float d, float z)
+{
+    return d * (phi_cdf_ref(z) + z * expf(-0.5f * z * z) * 0.39894228040143268f);
+}
+
+// bf16(d GELU'(z)).  The fast form's error is at most 2.5e-7 absolute in GELU',
+// as the reference form's is; it decides the rounding unless the value lies
+// within 64 FP32 ulps of a tie, where the reference does (about 1 value in 500).
+// Only where the two terms cancel (z near -0.75, |GELU'| below 0.04) can the two
+// forms round apart, by one unit of a value that small.  erfcf and expf on every
+// value cost the input gradients of layers 2 and 3 132 + 66 us, against 128 + 62
+// us, on 64 x 64 x 88.
 __device__ __forceinline__ uint32_t dgelu_bf16(float d, float z)
 {
-    return f2bf(d * (phi_cdf_ref(z) + z * expf(-0.5f * z * z) * 0.39894228040143268f));
+    float g;
+    const float p = phi_cdf_fast(z, g);
+    float v = d * fmaf(z * g, 0.39894228040143268f, p);
+    const uint32_t lo = __float_as_uint(v) & 0xFFFFu;
+    if (lo - 0x7FC0u < 0x80u || z < -13.0f) v = dgelu_ref(d, z);
+    return f2bf(v);
 }
 
 __device__ __forceinline__ bf16x8 as_bf(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
@@ -270,53 +285,109 @@ __device__ __forceinline__ u32x4 lds_a(const uint16_t *tile, int node, const uin
     return v;
 }
 
-// GELU epilogue of a forward layer with 32 output channels: lane (li, lg)
-// holds acc[r][h][j] of node (x0 + 4 lg + j, y0 + w, z0 + r), channel 16 h + li.
-// The activations go through LDS, so that the channel-last copy leaves as
-// whole 16-byte node parts and the channel-major copy as runs of consecutive
-// nodes, instead of one scattered 2-byte store per value.  `ot` holds
+// Where the four pre-activations a lane holds of row r, half h lie in zfrag: in
+// the order in which the lanes hold them, so that a wave reads and writes whole
+// kilobytes.  The forward layers and the input gradients use the same tiles;
+// the rows of a partial z tile are packed, so that the array has N x 32 values.
+__device__ __forceinline__ size_t zfrag_at(const Geo &g, int x0, int y0, int z0, int rows, int w, int r, int h, int lane)
+{
+    const int tile = x0 / TX + (g.nx / TX) * (y0 / TY);
+    return (size_t)g.nx * g.ny * z0 * 32 + (((size_t)tile * 4 + w) * rows + r) * 512 + h * 256 + lane * 4;
+}
+
+// Stores a block's 32-channel bf16 results: lane (li, lg) holds v[r][h][j] of
+// node (x0 + 4 lg + j, y0 + w, z0 + r), channel 16 h + li.  The channel-last
+// copy goes through LDS and leaves as whole 16-byte node parts; of the
+// channel-major copy a lane has four consecutive nodes, 8 bytes.  `ot` holds
 // TX * TY * TZ * 32 bf16 (16 KB) of LDS that no wave reads any more; tile-local
 // node l = (r TY + y) TX + x.
+__device__ __forceinline__ void store_bf16(const FwdArgs &a, const Geo &g, uint16_t *ot, const uint32_t (&v)[ROWS][2][4],
+                                           int x0, int y0, int z0, int rows, int w, int li, int lg)
+{
+    if (a.out_cm) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            if (r >= rows) continue;
+            const size_t node = (size_t)(x0 + 4 * lg) + (size_t)g.nx * ((y0 + w) + (size_t)g.ny * (z0 + r));
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                *(u32x2 *)(a.out_cm + (size_t)(16 * h + li) * g.N + node) =
+                    (u32x2){v[r][h][0] | v[r][h][1] << 16, v[r][h][2] | v[r][h][3] << 16};
+        }
+    }
+    if (!a.out_cl) return;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) ot[((r * TY + w) * TX + 4 * lg + j) * 32 + 16 * h + li] = (uint16_t)v[r][h][j];
+    __syncthreads();
+    constexpr int TN = TX * TY * TZ;
+    for (int q = threadIdx.x; q < TN * 4; q += 256) {
+        const int l = q >> 2, pt = q & 3;
+        const int x = l % TX, y = (l / TX) % TY, r = l / (TX * TY);
+        if (r < rows) {
+            const size_t node = (size_t)(x0 + x) + (size_t)g.nx * ((y0 + y) + (size_t)g.ny * (z0 + r));
+            *(u32x4 *)(a.out_cl + node * 32 + 8 * pt) = *(const u32x4 *)(ot + l * 32 + 8 * pt);
+        }
+    }
+}
+
+// GELU epilogue of a forward layer with 32 output channels, and the GELU'
+// epilogue of an input gradient, on the sums acc[r][h][j] held as v above.
+// 64 x 64 x 88 in training, where the pre-activations are kept and both copies
+// written: layer 1 43 -> 37 us, layer 2 111 -> 106 us, input gradients of layer 2
+// 128 -> 111 us and of layer 3 62 -> 46 us (before, the pre-activations moved as
+// single words and the copies as single bf16 values).
 __device__ __forceinline__ void gelu_epilogue(const FwdArgs &a, const Geo &g, uint16_t *ot, const f32x4 (&acc)[ROWS][2],
                                               int x0, int y0, int z0, int rows, int w, int li, int lg)
 {
-    __syncthreads();
+    uint32_t v[ROWS][2][4];
 #pragma unroll
     for (int r = 0; r < ROWS; ++r) {
         const int rowbase = g.nx * ((y0 + w) + g.ny * (z0 + r));
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int c = 16 * h + li;
+            f32x4 zz;
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
-                const float zz = acc[r][h][j] + a.bias[c];
-                ot[((r * TY + w) * TX + 4 * lg + j) * 32 + c] = (uint16_t)gelu_bf16(zz);
-                if (a.out_f32 && r < rows) a.out_f32[(size_t)(rowbase + x0 + 4 * lg + j) * 32 + c] = zz;
+                zz[j] = acc[r][h][j] + a.bias[c];
+                v[r][h][j] = gelu_bf16(zz[j]);
+                if (a.out_f32 && r < rows) a.out_f32[(size_t)(rowbase + x0 + 4 * lg + j) * 32 + c] = zz[j];
+            }
+            if (a.zfrag && r < rows) *(f32x4 *)(a.zfrag + zfrag_at(g, x0, y0, z0, rows, w, r, h, 16 * lg + li)) = zz;
+        }
+    }
+    store_bf16(a, g, ot, v, x0, y0, z0, rows, w, li, lg);
+}
+
+__device__ __forceinline__ void dgelu_epilogue(const FwdArgs &a, const Geo &g, uint16_t *ot, const f32x4 (&acc)[ROWS][2],
+                                               int x0, int y0, int z0, int rows, int w, int li, int lg)
+{
+    uint32_t v[ROWS][2][4];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) {
+        const int rowbase = g.nx * ((y0 + w) + g.ny * (z0 + min(r, rows - 1)));
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int c = 16 * h + li;
+            f32x4 zz;
+            if (a.zfrag)
+                zz = *(const f32x4 *)(a.zfrag + zfrag_at(g, x0, y0, z0, rows, w, min(r, rows - 1), h, 16 * lg + li));
+            else
+#pragma unroll
+                for (int j = 0; j < 4; ++j) zz[j] = a.zsave[(size_t)(rowbase + x0 + 4 * lg + j) * 32 + c];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                v[r][h][j] = dgelu_bf16(acc[r][h][j], zz[j]);
+                if (a.out_f32 && r < rows) a.out_f32[(size_t)(rowbase + x0 + 4 * lg + j) * 32 + c] = acc[r][h][j];
             }
         }
     }
-    __syncthreads();
-    constexpr int TN = TX * TY * TZ;
-    if (a.out_cl) {
-        for (int q = threadIdx.x; q < TN * 4; q += 256) {
-            const int l = q >> 2, pt = q & 3;
-            const int x = l % TX, y = (l / TX) % TY, r = l / (TX * TY);
-            if (r < rows) {
-                const size_t node = (size_t)(x0 + x) + (size_t)g.nx * ((y0 + y) + (size_t)g.ny * (z0 + r));
-                *(u32x4 *)(a.out_cl + node * 32 + 8 * pt) = *(const u32x4 *)(ot + l * 32 + 8 * pt);
-            }
-        }
-    }
-    if (a.out_cm) {
-        for (int q = threadIdx.x; q < TN * 32; q += 256) {
-            const int c = q / TN, l = q - c * TN;
-            const int x = l % TX, y = (l / TX) % TY, r = l / (TX * TY);
-            if (r < rows) {
-                const size_t node = (size_t)(x0 + x) + (size_t)g.nx * ((y0 + y) + (size_t)g.ny * (z0 + r));
-                a.out_cm[(size_t)c * g.N + node] = ot[l * 32 + c];
-            }
-        }
-    }
+    store_bf16(a, g, ot, v, x0, y0, z0, rows, w, li, lg);
 }
 
 // Layer 1 forward (1 -> 32 channels, GELU epilogue) and the input gradient of
@@ -397,29 +468,11 @@ __global__ __launch_bounds__(256) void k_conv_fwd(FwdArgs a)
         }
     }
 
-    if constexpr (EPI == EPI_GELU) {
-        __shared__ __attribute__((aligned(16))) uint16_t ot[TX * TY * TZ * 32];
+    __shared__ __attribute__((aligned(16))) uint16_t ot[TX * TY * TZ * 32];
+    if constexpr (EPI == EPI_GELU)
         gelu_epilogue(a, g, ot, acc, x0, y0, z0, rows, w, li, lg);
-    } else {
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            if (r >= rows) continue;
-            const int rowbase = g.nx * ((y0 + w) + g.ny * (z0 + r));
-#pragma unroll
-            for (int h = 0; h < NH; ++h) {
-                const int c = 16 * h + li;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int node = rowbase + x0 + 4 * lg + j;
-                    const float v = acc[r][h][j];
-                    const uint32_t bits = dgelu_bf16(v, a.zsave[(size_t)node * 32 + c]);
-                    if (a.out_f32) a.out_f32[(size_t)node * 32 + c] = v;
-                    if (a.out_cl) a.out_cl[(size_t)node * 32 + c] = (uint16_t)bits;
-                    if (a.out_cm) a.out_cm[(size_t)c * g.N + node] = (uint16_t)bits;
-                }
-            }
-        }
-    }
+    else
+        dgelu_epilogue(a, g, ot, acc, x0, y0, z0, rows, w, li, lg);
 }
 
 // Forward layer 2 (32 -> 32 channels, GELU) and its input gradient
@@ -503,29 +556,11 @@ __global__ __launch_bounds__(256, 4) void k_conv_fwd_split(FwdArgs a)
         }
     }
 
-    if constexpr (EPI == EPI_GELU) {
-        static_assert(TX * TY * TZ * 32 <= HNODES * 16, "the block's activations fit the halo buffer");
+    static_assert(TX * TY * TZ * 32 <= HNODES * 16, "the block's activations fit the halo buffer");
+    if constexpr (EPI == EPI_GELU)
         gelu_epilogue(a, g, tile, acc, x0, y0, z0, rows, w, li, lg);
-    } else {
-#pragma unroll
-        for (int r = 0; r < ROWS; ++r) {
-            if (r >= rows) continue;
-            const int rowbase = g.nx * ((y0 + w) + g.ny * (z0 + r));
-#pragma unroll
-            for (int h = 0; h < NH; ++h) {
-                const int c = 16 * h + li;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int node = rowbase + x0 + 4 * lg + j;
-                    const float v = acc[r][h][j];
-                    const uint32_t bits = dgelu_bf16(v, a.zsave[(size_t)node * 32 + c]);
-                    if (a.out_f32) a.out_f32[(size_t)node * 32 + c] = v;
-                    if (a.out_cl) a.out_cl[(size_t)node * 32 + c] = (uint16_t)bits;
-                    if (a.out_cm) a.out_cm[(size_t)c * g.N + node] = (uint16_t)bits;
-                }
-            }
-        }
-    }
+    else
+        dgelu_epilogue(a, g, tile, acc, x0, y0, z0, rows, w, li, lg);
 }
 
 // Layer 3 forward (32 -> 3 channels) with (output channel, dx) on the M
@@ -683,31 +718,24 @@ constexpr int WG_CHUNKS_TAP = 1024; // layer 1: waves = chunks
 // Layers 2 and 3: M = input channel (2 x 16), N = output channel (NB x 16),
 // K = nodes.  A block takes one dz and a run of lattice rows (a chunk), ten
 // waves: wave (dy, mi) the five dx taps of one dy and 16 input channels.  The
-// block marches along y, two rows a step: the input rows y - 2 .. y + 3 of
-// z + dz lie in a ring of eight LDS rows (with 8 nodes of x halo on either
-// side, periodic), so that each is loaded once for the 25 taps, and the two
-// rows of the output gradient in a double buffer; the next step's rows are
-// loaded during the products and written behind them, one barrier a step.  A
-// lane reads its 8 nodes and the two next to them once and forms the five
-// shifted operands by funnel shifts.  The rows' LDS strides are odd multiples
-// of 16 bytes (no bank conflicts among the 16 channels of a read).
-//   What bounds it: 64 x 64 x 88, layer 2 (92 GFLOP): the earlier kernel (a
-// wave per (dz, dy), operands straight from L2, 2.3 GB of it) took 349 us;
-// staged, the reads are 0.23 GB.
+// block marches along y, four rows a step: the input rows y - 2 .. y + 5 of
+// z + dz lie in a ring of sixteen LDS rows (with 8 nodes of x halo on either
+// side, periodic), so that each is loaded once for the 25 taps, and the four
+// rows of the output gradient in a double buffer.  A step's rows are loaded two
+// steps ahead and written to LDS behind the products of the step before it, one
+// barrier a step.  A lane reads its 8 nodes and the chunks on either side and
+// forms the five shifted operands by funnel shifts.  The rows' LDS strides are
+// odd multiples of 16 bytes (no bank conflicts among the 16 channels of a read).
+//   On 64 x 64 x 88, layer 2 (92 GFLOP) took 349 us with a wave per (dz, dy) and
+// its operands straight from L2 (2.3 GB of it), 129 us with two rows a step,
+// loaded one step ahead (each step then waits out a memory round trip), 104 us
+// now; layer 3, whose products fill 3 of the 16 columns, 254 -> 74 us.
 // partial[chunk][dz][dy][dx][32][16 NB]
-constexpr int WG_CHUNKS = 102;  // x 5 dz: two blocks per compute unit
-constexpr int WG_WAVES = 10, WG_RING = 8;
+constexpr int WG_CHUNKS = 51;  // x 5 dz: a block per compute unit
+constexpr int WG_WAVES = 10, WG_RING = 16, WG_ROWS = 4;
 
 // x tile of a row: 64 nodes where they divide it, else 32
 __host__ __device__ inline int wg_xt(const Geo &g) { return g.nx % 64 == 0 ? 64 : 32; }
-// row pairs a block of offset dz has to share with the others, and its first z
-__host__ __device__ inline int wg_pairs(const Geo &g, int dz, int &z0)
-{
-    const int a = dz < 0 ? -dz : dz;
-    z0 = g.zper || dz > 0 ? 0 : a;
-    const int zs = g.zper ? g.nz : (g.nz > a ? g.nz - a : 0);
-    return (g.nx / wg_xt(g)) * zs * (g.ny / 2);
-}
 
 template <int NB, int XT>
 __global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks, int cout, const uint16_t *__restrict__ actT,
@@ -715,10 +743,12 @@ __global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks,
 {
     constexpr int SA = XT + 24, SB = XT + 8;       // row strides in elements
     constexpr int CA = XT / 8 + 2, CB = XT / 8;    // 16-byte chunks of a row
-    constexpr int T = 64 * WG_WAVES;
+    constexpr int T = 64 * WG_WAVES, RS = WG_ROWS;
     __shared__ __attribute__((aligned(16))) uint16_t s_a[WG_RING][32][SA];
-    __shared__ __attribute__((aligned(16))) uint16_t s_b[2][2][16 * NB][SB];
-    const int dz = (int)blockIdx.x / chunks - 2, chunk = (int)blockIdx.x % chunks;
+    __shared__ __attribute__((aligned(16))) uint16_t s_b[2][RS][16 * NB][SB];
+    // the five dz of a chunk and neighbouring chunks on one XCD: they share rows
+    const int lb = xcd_block((int)blockIdx.x, (int)gridDim.x);
+    const int chunk = lb / 5, dz = lb - 5 * chunk - 2;
     const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int li = lane & 15, lg = lane >> 4;
     const int dy = w % 5 - 2, mi = w / 5;
@@ -729,92 +759,128 @@ __global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks,
         for (int nb = 0; nb < NB; ++nb) acc[d][nb] = (f32x4){0.f, 0.f, 0.f, 0.f};
     if constexpr (NB == 1) {
         // channels past cout stay zero
-        for (int q = threadIdx.x; q < 2 * 2 * 16 * NB * SB / 8; q += T) ((u32x4 *)s_b)[q] = (u32x4){0u, 0u, 0u, 0u};
+        for (int q = threadIdx.x; q < 2 * RS * 16 * NB * SB / 8; q += T) ((u32x4 *)s_b)[q] = (u32x4){0u, 0u, 0u, 0u};
     }
-
-    int zfirst;
-    const int pairs = wg_pairs(g, dz, zfirst), ph = g.ny / 2, zcount = g.zper ? g.nz : (g.nz > abs(dz) ? g.nz - abs(dz) : 0);
-    const int p0 = (int)((int64_t)pairs * chunk / chunks), p1 = (int)((int64_t)pairs * (chunk + 1) / chunks);
-    // pair p: segment p / (zcount ph), layer, rows 2 (p % ph) and the next
-    auto place = [&](int p, int &x0, int &z, int &y) {
-        const int col = p / ph;
-        y = 2 * (p - col * ph);
-        const int seg = col / zcount;
+    // layers z whose tap z + dz lies in the array, and this chunk's steps of them
+    const int zfirst = g.zper || dz > 0 ? 0 : -dz;
+    const int zcount = g.zper ? g.nz : max(0, g.nz - abs(dz));
+    const int ph = g.ny / RS, steps = (g.nx / XT) * zcount * ph;
+    const int p0 = (int)((int64_t)steps * chunk / chunks), p1 = (int)((int64_t)steps * (chunk + 1) / chunks);
+    // 16-byte chunks of the thread: of the step's four new input rows (halo
+    // included) and of its four output-gradient rows, at most two each
+    static_assert(RS * 32 * CA <= 2 * T && RS * 16 * NB * CB <= 2 * T, "two chunks per thread and step");
+    bool ha[2], hb[2];
+    int ac[2], arow[2], aoff[2], lao[2], boff[2], brow[2], lbo[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+        const int q = (int)threadIdx.x + k * T, ach = (q / CA) & 31, bch = (q / CB) % cout;
+        ha[k] = q < RS * 32 * CA;
+        hb[k] = q < RS * cout * CB;
+        ac[k] = q % CA;
+        arow[k] = q / (CA * 32);
+        aoff[k] = ach * g.N;
+        lao[k] = ach * SA + 8 * ac[k];
+        brow[k] = q / (CB * cout);
+        boff[k] = bch * g.N + 8 * (q % CB) + g.nx * brow[k];
+        lbo[k] = (brow[k] * 16 * NB + bch) * SB + 8 * (q % CB);
+    }
+    struct Rows {
+        u32x4 a[2], b[2];
+    };
+    // input rows Y .. Y + 3 of layer zs (-2 <= Y < ny + 8), gradient rows y .. y + 3
+    auto load_a = [&](Rows &v, int x0, int zs, int Y) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (ha[k])
+                v.a[k] = *(const u32x4 *)(actT + (size_t)aoff[k] +
+                                          (wrapi(x0 - 8 + 8 * ac[k], g.nx) +
+                                           g.nx * (mod_pos(Y + arow[k], g.ny) + g.ny * zs)));
+    };
+    auto load_b = [&](Rows &v, int x0, int z, int y) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (hb[k]) v.b[k] = *(const u32x4 *)(gT + (size_t)boff[k] + (x0 + g.nx * (y + g.ny * z)));
+    };
+    auto put_a = [&](const Rows &v, int Y) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (ha[k]) *(u32x4 *)(&s_a[0][0][0] + ((Y + arow[k]) & (WG_RING - 1)) * (32 * SA) + lao[k]) = v.a[k];
+    };
+    auto put_b = [&](const Rows &v, int buf) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+            if (hb[k]) *(u32x4 *)(&s_b[buf][0][0][0] + lbo[k]) = v.b[k];
+    };
+    int x0 = 0, z = 0, y = 0;
+    if (p0 < p1) {
+        const int col = p0 / ph, seg = col / zcount;
+        y = RS * (p0 - col * ph);
         x0 = seg * XT;
         z = zfirst + col - seg * zcount;
-    };
-    // 16-byte chunk k of the two input rows (Y, Y + 1) / output-gradient rows
-    auto load_a = [&](int k, int x0, int zs, int Y) -> u32x4 {
-        const int c = k % CA, ch = (k / CA) & 31, row = k / (CA * 32);
-        const int x = wrapi(x0 - 8 + 8 * c, g.nx);
-        return *(const u32x4 *)(actT + (size_t)ch * g.N + x + (size_t)g.nx * (mod_pos(Y + row, g.ny) + (size_t)g.ny * zs));
-    };
-    auto put_a = [&](int k, int Y, u32x4 v) {
-        const int c = k % CA, ch = (k / CA) & 31, row = k / (CA * 32);
-        *(u32x4 *)&s_a[(Y + row) & (WG_RING - 1)][ch][8 * c] = v;
-    };
-    auto load_b = [&](int k, int x0, int z, int y) -> u32x4 {
-        const int c = k % CB, ch = (k / CB) % cout, row = k / (CB * cout);
-        return *(const u32x4 *)(gT + (size_t)ch * g.N + x0 + 8 * c + (size_t)g.nx * (y + row + (size_t)g.ny * z));
-    };
-    auto put_b = [&](int k, int buf, u32x4 v) {
-        const int c = k % CB, ch = (k / CB) % cout, row = k / (CB * cout);
-        *(u32x4 *)&s_b[buf][row][ch][8 * c] = v;
-    };
-    constexpr int NA = 2 * 32 * CA;                 // chunks of two input rows: at most one per thread
-    static_assert(NA <= T && 2 * 16 * NB * CB <= T, "one chunk per thread and step");
-    const int nbk = 2 * cout * CB;
-    const int t = threadIdx.x;
-    bool fresh = true;
+    }
+    Rows v0, v1;  // the next step's rows, the one after's
     int buf = 0;
-    for (int p = p0; p < p1; ++p) {
-        int x0, z, y;
-        place(p, x0, z, y);
+    for (int p = p0; p < p1;) {
+        // a run: the steps of one column that belong to the chunk
+        const int n = min(p1 - p, (g.ny - y) / RS);
         const int zs = g.zper ? mod_pos(z + dz, g.nz) : z + dz;
-        if (fresh) {
-            // the first pair of a run: rows y - 2 .. y + 3 and the pair itself
-            __syncthreads();  // every wave is done with the ring
-            for (int r = 0; r < 3; ++r)
-                if (t < NA) put_a(t, y - 2 + 2 * r, load_a(t, x0, zs, y - 2 + 2 * r));
-            if (t < nbk) put_b(t, buf, load_b(t, x0, z, y));
-            __syncthreads();
+        load_a(v0, x0, zs, y - 2);
+        load_b(v0, x0, z, y);
+        load_a(v1, x0, zs, y + 2);
+        __syncthreads();  // every wave is done with the ring
+        put_a(v0, y - 2);
+        put_b(v0, buf);
+        put_a(v1, y + 2);
+        if (n > 1) {
+            load_a(v0, x0, zs, y + 6);
+            load_b(v0, x0, z, y + RS);
         }
-        // the next pair continues the run unless the layer (or the chunk) ends
-        const bool more = y + 2 < g.ny && p + 1 < p1;
-        u32x4 na = {0u, 0u, 0u, 0u}, nb_ = {0u, 0u, 0u, 0u};
-        if (more) {
-            if (t < NA) na = load_a(t, x0, zs, y + 4);
-            if (t < nbk) nb_ = load_b(t, x0, z, y + 2);
-        }
+        __syncthreads();
+        for (int i = 0; i < n; ++i) {
+            if (i + 2 < n) {
+                load_a(v1, x0, zs, y + 10);
+                load_b(v1, x0, z, y + 2 * RS);
+            }
 #pragma unroll
-        for (int row = 0; row < 2; ++row) {
-            const uint16_t *ra = &s_a[(y + row + dy) & (WG_RING - 1)][16 * mi + li][8];
+            for (int row = 0; row < RS; ++row) {
+                const uint16_t *ra = &s_a[(y + row + dy) & (WG_RING - 1)][16 * mi + li][8];
 #pragma unroll
-            for (int k = 0; k < XT / 32; ++k) {
-                const int x = 32 * k + 8 * lg;
-                bf16x8 bv[NB];
+                for (int k = 0; k < XT / 32; ++k) {
+                    const int x = 32 * k + 8 * lg;
+                    bf16x8 bv[NB];
 #pragma unroll
-                for (int nb = 0; nb < NB; ++nb) bv[nb] = as_bf(*(const u32x4 *)&s_b[buf][row][16 * nb + li][x]);
-                const u32x4 cur = *(const u32x4 *)(ra + x);
-                u32x4 prv, nxt;
-                prv[3] = *(const uint32_t *)(ra + x - 2);
-                nxt[0] = *(const uint32_t *)(ra + x + 8);
+                    for (int nb = 0; nb < NB; ++nb) bv[nb] = as_bf(*(const u32x4 *)&s_b[buf][row][16 * nb + li][x]);
+                    // whole chunks: single words at this stride would meet in
+                    // 16 of the banks
+                    const u32x4 cur = *(const u32x4 *)(ra + x);
+                    u32x4 prv = *(const u32x4 *)(ra + x - 8), nxt = *(const u32x4 *)(ra + x + 8);
+                    __asm__("" : "+v"(prv), "+v"(nxt));  // not narrowed to the words used
 #pragma unroll
-                for (int d = 0; d < 5; ++d) {
-                    const bf16x8 av = as_bf(shifted(prv, cur, nxt, d - 2));
+                    for (int d = 0; d < 5; ++d) {
+                        const bf16x8 av = as_bf(shifted(prv, cur, nxt, d - 2));
 #pragma unroll
-                    for (int nb = 0; nb < NB; ++nb)
-                        acc[d][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv[nb], acc[d][nb], 0, 0, 0);
+                        for (int nb = 0; nb < NB; ++nb)
+                            acc[d][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, bv[nb], acc[d][nb], 0, 0, 0);
+                    }
                 }
             }
-        }
-        if (more) {
-            if (t < NA) put_a(t, y + 4, na);
-            if (t < nbk) put_b(t, buf ^ 1, nb_);
-            __syncthreads();
+            if (i + 1 < n) {
+                put_a(v0, y + 6);
+                put_b(v0, buf ^ 1);
+                v0 = v1;
+                __syncthreads();
+            }
             buf ^= 1;
+            y += RS;
         }
-        fresh = !more;
+        p += n;
+        if (y == g.ny) {
+            y = 0;
+            if (++z == zfirst + zcount) {
+                z = zfirst;
+                x0 += XT;
+            }
+        }
     }
     float *out = partial + ((size_t)(chunk * 5 + dz + 2) * 25 + (size_t)(dy + 2) * 5) * 32 * 16 * NB;
 #pragma unroll
@@ -931,26 +997,40 @@ __device__ __forceinline__ double block_sum(double v, double *red)
 
 constexpr int COLSUM_CHUNKS = 64;
 
-// partial[c][chunk]
-__global__ __launch_bounds__(256) void k_colsum(Geo g, const uint16_t *__restrict__ gT, float *__restrict__ partial)
+__device__ __forceinline__ double wave_sum64(double v)
 {
-    __shared__ double red[4];
-    const int c = blockIdx.y, chunk = blockIdx.x;
-    const int per = (g.N + COLSUM_CHUNKS - 1) / COLSUM_CHUNKS;
-    const int n0 = chunk * per, n1 = min(g.N, n0 + per);
-    double s = 0.0;
-    for (int n = n0 + (int)threadIdx.x; n < n1; n += 256) s += (double)bf2f(gT[(size_t)c * g.N + n]);
-    const double t = block_sum(s, red);
-    if (threadIdx.x == 0) partial[c * COLSUM_CHUNKS + chunk] = (float)t;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) v += __shfl_down(v, off, 64);
+    return v;
 }
 
-__global__ void k_colsum_reduce(int nch, const float *__restrict__ partial, float *__restrict__ db)
+// Bias gradients of all layers at once: blocks (chunk, channel), the channels of
+// the three tensors in a row.  partial[c][chunk]
+__global__ __launch_bounds__(256) void k_colsum(Geo g, ColSums cs, float *__restrict__ partial)
 {
-    const int c = threadIdx.x;
-    if (c >= nch) return;
+    __shared__ double red[4];
+    int c = blockIdx.y, k = 0;
+    while (c >= cs.nch[k]) c -= cs.nch[k++];
+    const uint16_t *gT = cs.g[k] + (size_t)c * g.N;
+    const int chunk = blockIdx.x;
+    const int per = ((g.N + COLSUM_CHUNKS - 1) / COLSUM_CHUNKS + 7) / 8 * 8;  // N is a multiple of 128
+    const int n0 = chunk * per, n1 = min(g.N, n0 + per);
     double s = 0.0;
-    for (int k = 0; k < COLSUM_CHUNKS; ++k) s += (double)partial[c * COLSUM_CHUNKS + k];
-    db[c] = (float)s;
+    for (int n = n0 + 8 * (int)threadIdx.x; n < n1; n += 8 * 256) {
+        const u32x4 v = *(const u32x4 *)(gT + n);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) s += (double)bf2f(v[e] & 0xFFFFu) + (double)bf2f(v[e] >> 16);
+    }
+    const double t = block_sum(s, red);
+    if (threadIdx.x == 0) partial[blockIdx.y * COLSUM_CHUNKS + chunk] = (float)t;
+}
+
+__global__ void k_colsum_reduce(ColSums cs, const float *__restrict__ partial)
+{
+    int c = blockIdx.x, k = 0;
+    while (c >= cs.nch[k]) c -= cs.nch[k++];
+    const double t = wave_sum64((double)partial[blockIdx.x * COLSUM_CHUNKS + threadIdx.x]);
+    if (threadIdx.x == 0) cs.db[k][c] = (float)t;
 }
 
 // ------------------------------------------------------------ packing
@@ -1191,10 +1271,11 @@ hipError_t launch_wgrad(hipStream_t s, int layer, const Geo &g, const uint16_t *
 
 size_t colsum_partial_floats(const Geo &, int nch) { return (size_t)nch * COLSUM_CHUNKS; }
 
-hipError_t launch_colsum(hipStream_t s, const Geo &g, int nch, const uint16_t *gT, float *partial, float *db)
+hipError_t launch_colsum(hipStream_t s, const Geo &g, const ColSums &cs, float *partial)
 {
-    hipLaunchKernelGGL(k_colsum, dim3(COLSUM_CHUNKS, nch), dim3(256), 0, s, g, gT, partial);
-    hipLaunchKernelGGL(k_colsum_reduce, dim3(1), dim3(64), 0, s, nch, partial, db);
+    const int nch = cs.nch[0] + cs.nch[1] + cs.nch[2];
+    hipLaunchKernelGGL(k_colsum, dim3(COLSUM_CHUNKS, nch), dim3(256), 0, s, g, cs, partial);
+    hipLaunchKernelGGL(k_colsum_reduce, dim3(nch), dim3(COLSUM_CHUNKS), 0, s, cs, partial);
     return hipGetLastError();
 }
 

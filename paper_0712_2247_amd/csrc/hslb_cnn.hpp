@@ -8,7 +8,8 @@
 // Tensors (N = nx*ny*nz nodes, node = x + nx*(y + ny*z), no padding):
 //   x      bf16 [N]                     network input
 //   a1, a2 bf16 [N][32]  channel-last   activations (convolution inputs)
-//   z1, z2 fp32 [N][32]  channel-last   pre-activations (training only)
+//   z1, z2 fp32 [32 N]                  pre-activations (training only), in the order
+//                                       in which the forward kernels hold them
 //   *T     bf16 [32][N]  channel-major  copies for the weight gradients
 //   out    fp32 [3][N]                  F_hat
 //   d3     bf16 [N][4] / [3][N]         output gradient (4th channel 0)
@@ -59,7 +60,9 @@ struct FwdArgs {
     const uint16_t *in;    // CIN 1: [N]; 4: [N][4]; 32: [N][32]
     const uint16_t *wp;    // packed B operands
     const float *bias;     // [cout] (EPI_GELU, EPI_OUT)
-    const float *zsave;    // EPI_DGELU: pre-activation [N][32]
+    const float *zsave;    // EPI_DGELU: pre-activation [N][32] (without zfrag)
+    float *zfrag;          // pre-activations [32 N] in the kernels' own order (nullable):
+                           // EPI_GELU writes them, EPI_DGELU reads them
     uint16_t *out_cl;      // bf16 [N][32] (nullable)
     uint16_t *out_cm;      // bf16 [32][N] (nullable)
     float *out_f32;        // EPI_GELU: z [N][32]; EPI_OUT: [3][N]; EPI_DGELU: raw sum [N][32] (nullable)
@@ -76,10 +79,16 @@ hipError_t launch_conv_fwd(hipStream_t s, int cin, int cout, int epi, const FwdA
 size_t wgrad_partial_floats(const Geo &g, int layer);
 hipError_t launch_wgrad(hipStream_t s, int layer, const Geo &g, const uint16_t *src, const uint16_t *gT,
                         float *partial, float *dW);
-// db[c] = sum_n g[c][n] over channel-major bf16 gradients; `partial` holds
-// colsum_partial_floats(...) floats.
+// db[k][c] = sum_n g[k][c][n] over up to three channel-major bf16 gradients of
+// nch[k] channels (0: none); `partial` holds colsum_partial_floats(g, total
+// channels) floats.
+struct ColSums {
+    const uint16_t *g[3];
+    int nch[3];
+    float *db[3];
+};
 size_t colsum_partial_floats(const Geo &g, int nch);
-hipError_t launch_colsum(hipStream_t s, const Geo &g, int nch, const uint16_t *gT, float *partial, float *db);
+hipError_t launch_colsum(hipStream_t s, const Geo &g, const ColSums &cs, float *partial);
 
 // Packing of the canonical FP32 weights into the MFMA operand layouts.
 hipError_t launch_pack(hipStream_t s, int kind, const float *w, uint16_t *out);

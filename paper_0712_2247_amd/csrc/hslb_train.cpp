@@ -89,7 +89,7 @@ struct Work {
         size_t wp = 0;
         for (int l = 1; l <= 3; ++l) wp = std::max(wp, wgrad_partial_floats(g, l));
         const size_t o_wp = take(4 * wp);
-        const size_t o_cp = take(4 * colsum_partial_floats(g, 32));
+        const size_t o_cp = take(4 * colsum_partial_floats(g, 2 * CH + CO));
         nlpart = loss_blocks(g) + 64;
         const size_t o_lp = take(8 * nlpart);
         if (hipMalloc(&mem, off) != hipSuccess) return tfail(err, HSLB_ENOMEM, "training work buffers (%zu bytes)", off);
@@ -153,7 +153,7 @@ hipError_t forward(hipStream_t s, const Geo &g, const uint16_t *x, const float *
     a.bias = w + OB1;
     a.out_cl = wk.a1;
     a.out_cm = train ? wk.a1T : nullptr;
-    a.out_f32 = train ? wk.z1 : nullptr;
+    a.zfrag = train ? wk.z1 : nullptr;
     hipError_t e = launch_conv_fwd(s, 1, 32, EPI_GELU, a);
     if (e != hipSuccess) return e;
     a.in = wk.a1;
@@ -161,13 +161,14 @@ hipError_t forward(hipStream_t s, const Geo &g, const uint16_t *x, const float *
     a.bias = w + OB2;
     a.out_cl = wk.a2;
     a.out_cm = train ? wk.a2T : nullptr;
-    a.out_f32 = train ? wk.z2 : nullptr;
+    a.zfrag = train ? wk.z2 : nullptr;
     if ((e = launch_conv_fwd(s, 32, 32, EPI_GELU, a)) != hipSuccess) return e;
     a.in = wk.a2;
     a.wp = pk.p[PK_F3];
     a.bias = w + OB3;
     a.out_cl = nullptr;
     a.out_cm = nullptr;
+    a.zfrag = nullptr;
     a.out_f32 = wk.out;
     return launch_conv_fwd(s, 32, 3, EPI_OUT, a);
 }
@@ -179,23 +180,22 @@ hipError_t backward(hipStream_t s, const Geo &g, const uint16_t *x, const Packs 
     a.g = g;
     a.in = wk.d3cl;
     a.wp = pk.p[PK_D3];
-    a.zsave = wk.z2;
+    a.zfrag = wk.z2;
     a.out_cl = wk.dz2cl;
     a.out_cm = wk.dz2cm;
     hipError_t e = launch_conv_fwd(s, 4, 32, EPI_DGELU, a);
     if (e != hipSuccess) return e;
     a.in = wk.dz2cl;
     a.wp = pk.p[PK_D2];
-    a.zsave = wk.z1;
+    a.zfrag = wk.z1;
     a.out_cl = nullptr;
     a.out_cm = wk.dz1cm;
     if ((e = launch_conv_fwd(s, 32, 32, EPI_DGELU, a)) != hipSuccess) return e;
     if ((e = launch_wgrad(s, 3, g, wk.a2T, wk.d3cm, wk.wpart, grad + OW3)) != hipSuccess) return e;
-    if ((e = launch_colsum(s, g, CO, wk.d3cm, wk.cpart, grad + OB3)) != hipSuccess) return e;
     if ((e = launch_wgrad(s, 2, g, wk.a1T, wk.dz2cm, wk.wpart, grad + OW2)) != hipSuccess) return e;
-    if ((e = launch_colsum(s, g, CH, wk.dz2cm, wk.cpart, grad + OB2)) != hipSuccess) return e;
     if ((e = launch_wgrad(s, 1, g, x, wk.dz1cm, wk.wpart, grad + OW1)) != hipSuccess) return e;
-    return launch_colsum(s, g, CH, wk.dz1cm, wk.cpart, grad + OB1);
+    const ColSums cs{{wk.d3cm, wk.dz2cm, wk.dz1cm}, {CO, CH, CH}, {grad + OB3, grad + OB2, grad + OB1}};
+    return launch_colsum(s, g, cs, wk.cpart);
 }
 
 bool geo_ok(int nx, int ny, int nz) { return nx >= 32 && nx % 32 == 0 && ny >= 4 && ny % 4 == 0 && nz >= 1; }
@@ -581,7 +581,7 @@ int hslb_cnn_op(int32_t op, int32_t nx, int32_t ny, int32_t nz, int32_t zper, co
         const int ow = layer == 1 ? OW1 : (layer == 2 ? OW2 : OW3);
         const int ob = layer == 1 ? OB1 : (layer == 2 ? OB2 : OB3);
         T_TRY(launch_wgrad(s, layer, g, in_cm, aux_cm, wpart, gw + ow));
-        T_TRY(launch_colsum(s, g, c_aux, aux_cm, cpart, gw + ob));
+        T_TRY(launch_colsum(s, g, ColSums{{aux_cm, nullptr, nullptr}, {c_aux, 0, 0}, {gw + ob, nullptr, nullptr}}, cpart));
         const size_t nwl = (size_t)(ob - ow);
         T_TRY(hipMemcpyAsync(out, gw + ow, sizeof(float) * (nwl + c_aux), hipMemcpyDeviceToHost, s));
         T_TRY(hipStreamSynchronize(s));
