@@ -566,7 +566,8 @@ public:
         return launch("gfield", [&] { return launch_gfield<TM>(st(), L_, sc_.g2_model, fld_); });
     }
 
-    // whole x-rows per 256-thread block: moments and row sums in one launch
+    // whole x-rows per 256-thread block (39 velocities): moments and row sums in
+    // one launch
     bool fused_rows() const { return 256 % L_.nx == 0 && L_.plane % 256 == 0; }
 
     // Moments into the padded fields, for the readouts.
@@ -630,7 +631,7 @@ public:
                                                    aw, att_b);
             });
             if (rc) return rc;
-        } else if (sc_.hs_on && fused_rows()) {
+        } else if (sc_.hs_on && moments_rs_apply(L_)) {
             rc = launch("moments", [&] {
                 return launch_moments_rs<TF, TM>(st(), L_, sigma_, nref_d_, f_[cur_], fld_, rs_, sc_.phi != nullptr);
             });

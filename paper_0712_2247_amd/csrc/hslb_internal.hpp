@@ -153,11 +153,12 @@ hipError_t launch_moments(hipStream_t s, const LatticeDev &L, const double *nref
                           Fields<TM> fld);
 template <typename TM>
 hipError_t launch_gfield(hipStream_t s, const LatticeDev &L, int g2_model, Fields<TM> fld);
-// Moments plus the row sums of the two-pass ball sum in one launch; returns
-// hipErrorInvalidValue (launching nothing) unless nx divides 256 and the plane
-// is a multiple of 256.  Then launch_ballsum completes eta_bar.  write_n: also
-// the separate density field fld.n (the interleaved (n, j) is always written;
-// within a step only the attraction reads fld.n).
+// Moments plus the row sums of the two-pass ball sum in one launch, for
+// moments_rs_apply lattices (nx <= 512; others: hipErrorInvalidValue, launching
+// nothing).  Then launch_ballsum completes eta_bar.  write_n: also the separate
+// density field fld.n (the interleaved (n, j) is always written; within a step
+// only the attraction reads fld.n).
+bool moments_rs_apply(const LatticeDev &L);
 template <typename TF, typename TM>
 hipError_t launch_moments_rs(hipStream_t s, const LatticeDev &L, int sigma, const double *nref, const TF *f,
                              Fields<TM> fld, TM *rs, bool write_n);
@@ -231,8 +232,8 @@ hipError_t launch_copy(hipStream_t s, const void *src, void *dst, size_t bytes);
 hipError_t launch_feq39(hipStream_t s, const LatticeDev &L, const double *n, const double *u, const double *T,
                         double *out);
 hipError_t launch_moments39(hipStream_t s, const LatticeDev &L, const double *f, Fields<double> fld, bool thermal);
-// The same fused with the ball sum's row sums (as launch_moments_rs: nx divides
-// 256 and the plane is a multiple of 256, else hipErrorInvalidValue).
+// The same fused with the ball sum's row sums (nx divides 256 and the plane is a
+// multiple of 256, else hipErrorInvalidValue).
 hipError_t launch_moments39_rs(hipStream_t s, const LatticeDev &L, int sigma, const double *f, Fields<double> fld,
                                bool thermal, double *rs);
 hipError_t launch_collide39(hipStream_t s, const LatticeDev &L, int sigma, const StepConst &c, const double *chi,

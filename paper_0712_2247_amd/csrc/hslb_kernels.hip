@@ -311,6 +311,23 @@ __global__ __launch_bounds__(256) void k_moments_rs(LatticeDev L, const double *
     block_rowsums<SIG>(L, sn, rs, z, r, nt != 0);
 }
 
+// The same for rows that do not tile 256 nodes: blockDim.x / nx whole rows per
+// block, its last threads idle (see moments_rows_block).
+template <int SIG, typename TF, typename TM>
+__global__ __launch_bounds__(512) void k_moments_rows(LatticeDev L, const double *__restrict__ nref,
+                                                      const TF *__restrict__ f, Fields<TM> fld, TM *__restrict__ rs,
+                                                      int write_n, int nt)
+{
+    __shared__ TM sn[512];
+    const int t = threadIdx.x, nodes = (int)blockDim.x / L.nx * L.nx;
+    const int r = (int)blockIdx.x * nodes + t;
+    const int z = (int)blockIdx.y;
+    const bool act = t < nodes && r < L.plane;
+    if (act) sn[t] = d_moments(L, nref, f, fld, z, r, write_n != 0, nt != 0);
+    __syncthreads();
+    if (act) block_rowsums<SIG>(L, sn, rs, z, r, nt != 0);
+}
+
 // Row sums rs[w], w = 0..R, of node r of layer z from the block's densities in
 // LDS (the block holds whole x-rows of the layer), written at the padded layer
 // of z and, for a periodic z axis, at its images within the padded range the
@@ -1285,7 +1302,8 @@ __device__ __forceinline__ void d_collide(const LatticeDev &L, const StepConst &
             const double *rw = layer_ref(sc.nref_w, z);
 #pragma unroll
             for (int i = 0; i < NQ; ++i) fout[(size_t)i * L.pop_stride + id] = (TF)(0.0 - rw[i]);
-            return;
+            // lanes that share reads need this one in the shell sum (of zeros)
+            if constexpr (ROT == 0) return;
         }
     }
     // the stored values are kept through the shell sum (half the registers of
@@ -1327,6 +1345,7 @@ __device__ __forceinline__ void d_collide(const LatticeDev &L, const StepConst &
     const double u[3] = {jx * inv_n, jy * inv_n, jz * inv_n};
     double Fv[3];
     node_force<SIG, LZ, TM, MASK, STAGED, ROT>(fld, L, sc, chi, x, y, z, n, u, Fv, tile);
+    if (MASK && ROT != 0 && (lk & LINK_SOLID)) return;
 
     // BGK relaxation (10) towards the equilibrium (11), with the first-order
     // source, for opposite velocities i and i + 1 together: with cu = c_i.u,
@@ -3566,25 +3585,57 @@ hipError_t launch_smooth2(hipStream_t s, const LatticeDev &L, int sigma, double 
     return hipGetLastError();
 }
 
+// Threads of a block of k_moments_rows: the size up to 512 that leaves the
+// fewest threads idle (whole rows per block, whole blocks per layer).  100x72x90
+// slit, sigma 5, FP32: moments and row sums 9.7 + 5.6 -> 11 us.
+inline int moments_rows_block(const LatticeDev &L)
+{
+    int best = 0;
+    double eff = 0.0;
+    for (int t = 64; t <= 512; t += 64) {
+        const int rows = t / L.nx;
+        if (!rows) continue;
+        const double e = (double)L.plane / ((double)((L.ny + rows - 1) / rows) * t);
+        if (e > eff * 1.02) {
+            eff = e;
+            best = t;
+        }
+    }
+    return best;
+}
+
+bool moments_rs_apply(const LatticeDev &L) { return (256 % L.nx == 0 && L.plane % 256 == 0) || L.nx <= 512; }
+
 template <typename TF, typename TM>
 hipError_t launch_moments_rs(hipStream_t s, const LatticeDev &L, int sigma, const double *nref, const TF *f,
                              Fields<TM> fld, TM *rs, bool write_n)
 {
-    if (256 % L.nx != 0 || L.plane % 256 != 0) return hipErrorInvalidValue;
-    const dim3 g(L.plane / 256, L.nz), b(256);
+    if (!moments_rs_apply(L)) return hipErrorInvalidValue;
+    const bool tiled = 256 % L.nx == 0 && L.plane % 256 == 0;
+    const int t = tiled ? 256 : moments_rows_block(L);
+    const int rows = t / L.nx;
+    const dim3 g(tiled ? L.plane / 256 : (L.ny + rows - 1) / rows, L.nz), b(t);
     // (n, j) and the row sums beyond the 256 MiB last-level cache are stored
     // non-temporally, as the contact values are (256^3 bulk: 282 MB each)
     const int nt = 4.0 * sizeof(TM) * (double)L.fld_stride > HSLB_NT_FIELD_MIB * 1024.0 * 1024.0 ? 1 : 0;
+#define HSLB_MRS(SG)                                                                                             \
+    case SG:                                                                                                     \
+        if (tiled)                                                                                               \
+            hipLaunchKernelGGL((k_moments_rs<SG, TF, TM>), g, b, 0, s, L, nref, f, fld, rs, (int)write_n, nt);   \
+        else                                                                                                     \
+            hipLaunchKernelGGL((k_moments_rows<SG, TF, TM>), g, b, 0, s, L, nref, f, fld, rs, (int)write_n, nt); \
+        break;
     switch (sigma) {
-    case 2: hipLaunchKernelGGL((k_moments_rs<2, TF, TM>), g, b, 0, s, L, nref, f, fld, rs, (int)write_n, nt); break;
-    case 3: hipLaunchKernelGGL((k_moments_rs<3, TF, TM>), g, b, 0, s, L, nref, f, fld, rs, (int)write_n, nt); break;
-    case 4: hipLaunchKernelGGL((k_moments_rs<4, TF, TM>), g, b, 0, s, L, nref, f, fld, rs, (int)write_n, nt); break;
-    case 5: hipLaunchKernelGGL((k_moments_rs<5, TF, TM>), g, b, 0, s, L, nref, f, fld, rs, (int)write_n, nt); break;
-    case 6: hipLaunchKernelGGL((k_moments_rs<6, TF, TM>), g, b, 0, s, L, nref, f, fld, rs, (int)write_n, nt); break;
-    case 7: hipLaunchKernelGGL((k_moments_rs<7, TF, TM>), g, b, 0, s, L, nref, f, fld, rs, (int)write_n, nt); break;
-    case 8: hipLaunchKernelGGL((k_moments_rs<8, TF, TM>), g, b, 0, s, L, nref, f, fld, rs, (int)write_n, nt); break;
+        HSLB_MRS(2)
+        HSLB_MRS(3)
+        HSLB_MRS(4)
+        HSLB_MRS(5)
+        HSLB_MRS(6)
+        HSLB_MRS(7)
+        HSLB_MRS(8)
     default: return hipErrorInvalidValue;
     }
+#undef HSLB_MRS
     return hipGetLastError();
 }
 
@@ -3671,7 +3722,11 @@ hipError_t launch_collide(hipStream_t s, const LatticeDev &L, int sigma, const S
     // (sigma 8, 8-row bands) keeps z slabs, 39.6 against 41.9 us.  Splitting
     // each band's layers over 2 or 4 XCDs (wider bands) measured in between.
     const int band = (cpp % 8 == 0 && L.ny >= 16 * sigma) ? 1 : 0;
-    if (c.links) return launch_collide_t<TF, TM, true, false>(s, sigma, g, b, L, c, chi, fin, fout, fld, cpp, band);
+    if (c.links) {
+        if (L.nx == 64)
+            return launch_collide_t<TF, TM, true, false, 1>(s, sigma, g, b, L, c, chi, fin, fout, fld, cpp, band);
+        return launch_collide_t<TF, TM, true, false>(s, sigma, g, b, L, c, chi, fin, fout, fld, cpp, band);
+    }
     // populations beyond the last-level cache (two copies over 128 MiB) stream
     // non-temporally
     const double pop_bytes = 2.0 * NQ * (double)L.pop_stride * sizeof(TF);
@@ -3688,14 +3743,16 @@ hipError_t launch_collide(hipStream_t s, const LatticeDev &L, int sigma, const S
             if ((L.nx == 128 || L.nx == 256) && L.plane % 256 == 0 && sigma >= 2)
                 return launch_collide_t<TF, TM, false, true, 3>(s, sigma, g, b, L, c, chi, fin, fout, fld, cpp, band);
         }
+        if (L.nx == 64)
+            return launch_collide_t<TF, TM, false, true, 1>(s, sigma, g, b, L, c, chi, fin, fout, fld, cpp, band);
         return launch_collide_t<TF, TM, false, true>(s, sigma, g, b, L, c, chi, fin, fout, fld, cpp, band);
     }
     // a wave per x-row of 64 nodes: x-neighbour (n, j) reads shared between
-    // lanes (benchmark slit 39.9 -> 36.7 us)
-    if constexpr (std::is_same<TF, float>::value && std::is_same<TM, float>::value) {
-        if (L.nx == 64)
-            return launch_collide_t<TF, TM, false, false, 1>(s, sigma, g, b, L, c, chi, fin, fout, fld, cpp, band);
-    }
+    // lanes (benchmark slit 39.9 -> 36.7 us; per step, with a solid cylinder 71
+    // -> 66 us, FP64 storage 116.5 -> 108.8 us, 64x64x400 FP32 157 -> 151 us; the
+    // thermal 39-velocity collide lost from it, 110 -> 119 us)
+    if (L.nx == 64)
+        return launch_collide_t<TF, TM, false, false, 1>(s, sigma, g, b, L, c, chi, fin, fout, fld, cpp, band);
     return launch_collide_t<TF, TM, false, false>(s, sigma, g, b, L, c, chi, fin, fout, fld, cpp, band);
 }
 
