@@ -1455,9 +1455,9 @@ __device__ __forceinline__ void d_collide(const LatticeDev &L, const StepConst &
 // than by layer-uniform base offsets: 1513 against 1530 us on the bulk, while
 // the slit keeps the layer-uniform form (39.5 against 40.8 us).
 template <int SIG, typename TF, typename TM, bool MASK, bool NT, int ROT>
-__global__ __launch_bounds__(256, HSLB_COLLIDE_WAVES) void k_collide(LatticeDev L, StepConst sc, const double *__restrict__ chi,
-                                                 const TF *__restrict__ fin, TF *__restrict__ fout,
-                                                 Fields<TM> fld, int cpp, int band)
+__device__ __forceinline__ void collide_block(const LatticeDev &L, const StepConst &sc, const double *__restrict__ chi,
+                                              const TF *__restrict__ fin, TF *__restrict__ fout, const Fields<TM> &fld,
+                                              int cpp, int band)
 {
     int zl, c;
     if (band) {
@@ -1477,6 +1477,30 @@ __global__ __launch_bounds__(256, HSLB_COLLIDE_WAVES) void k_collide(LatticeDev 
         __syncthreads();
     }
     if (r < L.plane) d_collide<SIG, !NT, TF, TM, MASK, NT, false, ROT>(L, sc, chi, fin, fout, fld, z, r);
+}
+
+// The kernel proper, capped at 128 registers (the attribute counts them in
+// pairs), so that 4 waves share a SIMD: scheduled for 3 waves it takes 128 to
+// 138 otherwise, and which side of 128 it falls on decides 4 waves or 3.  The
+// cap costs up to 6 spilled registers; scheduling for 4 waves (104 to 122
+// registers, its loads closer to their uses) is slower than either.  Per step:
+// 100x72x90 slit FP32 72.3 -> 70.3 us, 64x64x136 slit with FP64 storage
+// 116.8 -> 109.0 us, 256^3 bulk 1942 -> 1935 us.  The cache-resident FP64
+// instances lose (100x60x40 56.7 -> 57.9 us) and go without (k_collide_free).
+template <int SIG, typename TF, typename TM, bool MASK, bool NT, int ROT>
+__global__ __launch_bounds__(256, HSLB_COLLIDE_WAVES) __attribute__((amdgpu_num_vgpr(64))) void k_collide(
+    LatticeDev L, StepConst sc, const double *__restrict__ chi, const TF *__restrict__ fin, TF *__restrict__ fout,
+    Fields<TM> fld, int cpp, int band)
+{
+    collide_block<SIG, TF, TM, MASK, NT, ROT>(L, sc, chi, fin, fout, fld, cpp, band);
+}
+
+template <int SIG, typename TF, typename TM, bool MASK, bool NT, int ROT>
+__global__ __launch_bounds__(256, HSLB_COLLIDE_WAVES) void k_collide_free(
+    LatticeDev L, StepConst sc, const double *__restrict__ chi, const TF *__restrict__ fin, TF *__restrict__ fout,
+    Fields<TM> fld, int cpp, int band)
+{
+    collide_block<SIG, TF, TM, MASK, NT, ROT>(L, sc, chi, fin, fout, fld, cpp, band);
 }
 
 // k_collide for FP32 storage and fields with the shell sum staged through LDS:
@@ -3760,17 +3784,27 @@ template <typename TF, typename TM, bool M, bool NT, int ROT>
 hipError_t launch_collide_t(hipStream_t s, int sigma, dim3 g, dim3 b, const LatticeDev &L, const StepConst &c,
                             const double *chi, const TF *fin, TF *fout, Fields<TM> fld, int cpp, int band)
 {
+    constexpr bool cap = sizeof(TF) == 4 || NT;  // see k_collide
+#define HSLB_CO(SG)                                                                                                    \
+    case SG:                                                                                                           \
+        if constexpr (cap)                                                                                             \
+            hipLaunchKernelGGL((k_collide<SG, TF, TM, M, NT, ROT>), g, b, 0, s, L, c, chi, fin, fout, fld, cpp, band); \
+        else                                                                                                           \
+            hipLaunchKernelGGL((k_collide_free<SG, TF, TM, M, NT, ROT>), g, b, 0, s, L, c, chi, fin, fout, fld, cpp,   \
+                               band);                                                                                  \
+        break;
     switch (sigma) {
-    case 0: hipLaunchKernelGGL((k_collide<0, TF, TM, M, NT, ROT>), g, b, 0, s, L, c, chi, fin, fout, fld, cpp, band); break;
-    case 2: hipLaunchKernelGGL((k_collide<2, TF, TM, M, NT, ROT>), g, b, 0, s, L, c, chi, fin, fout, fld, cpp, band); break;
-    case 3: hipLaunchKernelGGL((k_collide<3, TF, TM, M, NT, ROT>), g, b, 0, s, L, c, chi, fin, fout, fld, cpp, band); break;
-    case 4: hipLaunchKernelGGL((k_collide<4, TF, TM, M, NT, ROT>), g, b, 0, s, L, c, chi, fin, fout, fld, cpp, band); break;
-    case 5: hipLaunchKernelGGL((k_collide<5, TF, TM, M, NT, ROT>), g, b, 0, s, L, c, chi, fin, fout, fld, cpp, band); break;
-    case 6: hipLaunchKernelGGL((k_collide<6, TF, TM, M, NT, ROT>), g, b, 0, s, L, c, chi, fin, fout, fld, cpp, band); break;
-    case 7: hipLaunchKernelGGL((k_collide<7, TF, TM, M, NT, ROT>), g, b, 0, s, L, c, chi, fin, fout, fld, cpp, band); break;
-    case 8: hipLaunchKernelGGL((k_collide<8, TF, TM, M, NT, ROT>), g, b, 0, s, L, c, chi, fin, fout, fld, cpp, band); break;
+        HSLB_CO(0)
+        HSLB_CO(2)
+        HSLB_CO(3)
+        HSLB_CO(4)
+        HSLB_CO(5)
+        HSLB_CO(6)
+        HSLB_CO(7)
+        HSLB_CO(8)
     default: return hipErrorInvalidValue;
     }
+#undef HSLB_CO
     return hipGetLastError();
 }
 
