@@ -1,14 +1,16 @@
 // HIP kernels of the hard-sphere lattice Boltzmann step for gfx950.
 //
-// One step (equation (10) of the paper) runs as five kernels on the stream:
-//   k_moments  populations -> n, j                      (equation (8))
-//   k_rowsum,  n -> coarse-grained packing fraction      (ball of radius sigma/2,
-//   k_ballsum     as row-segment sums: two passes)
-//   k_gfield   eta_bar -> contact values g2 on the 7 sub-lattices of pair
-//              midpoints (lattice nodes, edge, face centres)
-//   k_collide  shell-sum force C^(1) of equation (12) + n g, BGK collision with
-//              the second-order equilibrium (11) and first-order source, push
-//              streaming with halfway bounce-back
+// One step (equation (10) of the paper) runs on the stream as
+//   k_moments_rs,  populations -> n, j (equation (8)) and the row sums of the
+//   k_moments_rows   ball sum (k_moments and k_rowsum where a block cannot hold
+//                    whole x-rows)
+//   k_ballsum      row sums -> coarse-grained packing fraction eta_bar
+//   k_gfield       eta_bar -> contact values g2 on the 7 sub-lattices of pair
+//                  midpoints (lattice nodes, edge, face centres)
+//   k_collide      shell-sum force C^(1) of equation (12) + n g, BGK collision with
+//                  the second-order equilibrium (11) and first-order source, push
+//                  streaming with halfway bounce-back
+// and on a small lattice as k_fields_small and k_collide_split.
 //
 // Storage: populations SoA [19][pop_stride] in TF (float or double), kept
 // relative to the layer means of each population (a per-layer reference table,
@@ -1434,10 +1436,10 @@ __device__ __forceinline__ void d_collide(const LatticeDev &L, const StepConst &
     }
 }
 
-// Waves per SIMD the collide kernel is compiled for (register budget
-// 512 / waves).  3 leaves the compiler its natural ~130 VGPRs; 4 and 5
-// (104 and 96 VGPRs, no spills) measured 25 % slower: the shell reads of more
-// resident waves overflow the L1.
+// Waves per SIMD the collide kernel is scheduled for (register budget
+// 512 / waves).  3 leaves the compiler its natural ~130 VGPRs; scheduled for 4
+// and 5 (104 and 96 VGPRs, no spills) it measured 25 % slower.  k_collide caps
+// the registers of the 3-wave schedule at 128 (see there).
 #ifndef HSLB_COLLIDE_WAVES
 #define HSLB_COLLIDE_WAVES 3
 #endif
@@ -1573,10 +1575,14 @@ __global__ __launch_bounds__(256) void k_force(LatticeDev L, StepConst sc, const
 //                    block that needs them and kept in LDS;
 //   k_collide_split  64 nodes per block, six waves: each takes one face-diagonal
 //                    point of the shell (and three of them an axis pair), then
-//                    three or four of the 19 directions.  A wave then waits for
+//                    two to four of the 19 directions.  A wave then waits for
 //                    about 30 loads instead of 127.
 // Every sum is formed in the order of the general kernels, so the results are
-// bit for bit theirs.
+// bit for bit theirs (the attraction's aside, whose potential rounds apart).
+// Kernel times (rocprofv3), before -> now: 8x8x24 sigma 4 FP64 3.6 + 2.0 + 2.2 +
+// 2.7 + collide 9.4 -> 5.1 + 4.9 us; 16x16x128 sigma 4 FP64 with the attraction
+// 4.9 + 3.4 + 3.8 + 10.4 + 14.2 -> 11.7 + 10.1 us; 24x20x30 sigma 8, the force of
+// (n, u): nine launches, 38 us -> 12.3 + 5.4 us, 16 us a call back to back.
 
 // Sources of the density and current of a node: stored populations with their
 // reference table, or the fields (n, u) themselves (the rest state without u;
@@ -3611,7 +3617,7 @@ hipError_t launch_smooth2(hipStream_t s, const LatticeDev &L, int sigma, double 
 
 // Threads of a block of k_moments_rows: the size up to 512 that leaves the
 // fewest threads idle (whole rows per block, whole blocks per layer).  100x72x90
-// slit, sigma 5, FP32: moments and row sums 9.7 + 5.6 -> 11 us.
+// slit, sigma 5, FP32: moments and row sums 9.7 + 5.6 -> 11.7 us.
 inline int moments_rows_block(const LatticeDev &L)
 {
     int best = 0;
