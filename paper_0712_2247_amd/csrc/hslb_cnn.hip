@@ -728,10 +728,17 @@ constexpr int WG_CHUNKS_TAP = 1024; // layer 1: waves = chunks
 // odd multiples of 16 bytes (no bank conflicts among the 16 channels of a read).
 //   On 64 x 64 x 88, layer 2 (92 GFLOP) took 349 us with a wave per (dz, dy) and
 // its operands straight from L2 (2.3 GB of it), 129 us with two rows a step,
-// loaded one step ahead (each step then waits out a memory round trip), 104 us
-// now; layer 3, whose products fill 3 of the 16 columns, 254 -> 74 us.
-// partial[chunk][dz][dy][dx][32][16 NB]
+// loaded one step ahead (each step then waits out a memory round trip), 102 us
+// now; layer 3, whose products fill 3 of the 16 columns, 254 -> 72 us.
+//   A chunk is summed in two halves, each from zero, and the halves meet in the
+// FP64 sum of the reduction: one FP32 chain over the whole chunk is longer than
+// that of the 64 chunks which a wave per (dz, dy) took, and its rounding larger
+// (rms against FP64 sums, layer 2 on 64 x 64 x 88: 64 chunks 4.7e-7, 51 chunks
+// 5.3e-7, 51 chunks in halves 3.6e-7 of the gradient's rms; the whole gradient
+// takes 2 % longer, 637 -> 652 us, for the reduction's second 26 MB).
+// partial[chunk][half][dz][dy][dx][32][16 NB]
 constexpr int WG_CHUNKS = 51;  // x 5 dz: a block per compute unit
+constexpr int WG_PARTS = 2 * WG_CHUNKS;
 constexpr int WG_WAVES = 10, WG_RING = 16, WG_ROWS = 4;
 
 // x tile of a row: 64 nodes where they divide it, else 32
@@ -819,7 +826,20 @@ __global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks,
         z = zfirst + col - seg * zcount;
     }
     Rows v0, v1;  // the next step's rows, the one after's
-    int buf = 0;
+    int buf = 0, half = 0;
+    const int pm = (p0 + p1 + 1) / 2;  // first step of the second half
+    auto flush = [&](int h) {
+        float *out = partial + ((size_t)((2 * chunk + h) * 5 + dz + 2) * 25 + (size_t)(dy + 2) * 5) * 32 * 16 * NB;
+#pragma unroll
+        for (int d = 0; d < 5; ++d)
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    out[((size_t)d * 32 + 16 * mi + 4 * lg + j) * 16 * NB + 16 * nb + li] = acc[d][nb][j];
+                acc[d][nb] = (f32x4){0.f, 0.f, 0.f, 0.f};
+            }
+    };
     for (int p = p0; p < p1;) {
         // a run: the steps of one column that belong to the chunk
         const int n = min(p1 - p, (g.ny - y) / RS);
@@ -837,6 +857,10 @@ __global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks,
         }
         __syncthreads();
         for (int i = 0; i < n; ++i) {
+            if (p + i == pm) {
+                flush(0);
+                half = 1;
+            }
             if (i + 2 < n) {
                 load_a(v1, x0, zs, y + 10);
                 load_b(v1, x0, z, y + 2 * RS);
@@ -882,17 +906,11 @@ __global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks,
             }
         }
     }
-    float *out = partial + ((size_t)(chunk * 5 + dz + 2) * 25 + (size_t)(dy + 2) * 5) * 32 * 16 * NB;
-#pragma unroll
-    for (int d = 0; d < 5; ++d)
-#pragma unroll
-        for (int nb = 0; nb < NB; ++nb)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                out[((size_t)d * 32 + 16 * mi + 4 * lg + j) * 16 * NB + 16 * nb + li] = acc[d][nb][j];
+    flush(half);
+    if (half == 0) flush(1);  // a chunk of one step or none: the second half is empty
 }
 
-// dW[co][ci][t] = sum over chunks; threads run over co fastest, then ci, so
+// dW[co][ci][t] = sum over the chunks' halves; threads run over co fastest, then ci, so
 // that neighbouring threads read neighbouring partials
 __global__ __launch_bounds__(256) void k_wgrad_ch_reduce(int chunks, int nb16, int cout, const float *__restrict__ partial,
                                                          float *__restrict__ dW)
@@ -1237,7 +1255,7 @@ hipError_t launch_conv_fwd(hipStream_t s, int cin, int cout, int epi, const FwdA
 size_t wgrad_partial_floats(const Geo &g, int layer)
 {
     if (layer == 1) return (size_t)row_split(g, WG_CHUNKS_TAP).chunks * 128 * 32;
-    return (size_t)WG_CHUNKS * NT * 32 * 16 * (layer == 2 ? 2 : 1);
+    return (size_t)WG_PARTS * NT * 32 * 16 * (layer == 2 ? 2 : 1);
 }
 
 template <int NB>
@@ -1261,10 +1279,10 @@ hipError_t launch_wgrad(hipStream_t s, int layer, const Geo &g, const uint16_t *
     }
     if (layer == 2) {
         launch_wgrad_rows<2>(s, g, CH, src, gT, partial);
-        hipLaunchKernelGGL(k_wgrad_ch_reduce, dim3(nblocks(CH * 32 * NT)), dim3(256), 0, s, WG_CHUNKS, 32, CH, partial, dW);
+        hipLaunchKernelGGL(k_wgrad_ch_reduce, dim3(nblocks(CH * 32 * NT)), dim3(256), 0, s, WG_PARTS, 32, CH, partial, dW);
     } else {
         launch_wgrad_rows<1>(s, g, CO, src, gT, partial);
-        hipLaunchKernelGGL(k_wgrad_ch_reduce, dim3(nblocks(CO * 32 * NT)), dim3(256), 0, s, WG_CHUNKS, 16, CO, partial, dW);
+        hipLaunchKernelGGL(k_wgrad_ch_reduce, dim3(nblocks(CO * 32 * NT)), dim3(256), 0, s, WG_PARTS, 16, CO, partial, dW);
     }
     return hipGetLastError();
 }
