@@ -20,6 +20,7 @@
 #include "hslb_cnn.hpp"
 #include "hslb_internal.hpp"
 
+#include <algorithm>
 #include <cmath>
 
 namespace hslb {
@@ -718,10 +719,10 @@ constexpr int WG_CHUNKS_TAP = 1024; // layer 1: waves = chunks
 // Layers 2 and 3: M = input channel (2 x 16), N = output channel (NB x 16),
 // K = nodes.  A block takes one dz and a run of lattice rows (a chunk), ten
 // waves: wave (dy, mi) the five dx taps of one dy and 16 input channels.  The
-// block marches along y, four rows a step: the input rows y - 2 .. y + 5 of
-// z + dz lie in a ring of sixteen LDS rows (with 8 nodes of x halo on either
-// side, periodic), so that each is loaded once for the 25 taps, and the four
-// rows of the output gradient in a double buffer.  A step's rows are loaded two
+// block marches along y, four rows a step (one on small lattices): the input rows
+// y - 2 .. y + 5 of z + dz lie in a ring of sixteen LDS rows (with 8 nodes of x
+// halo on either side, periodic), so that each is loaded once for the 25 taps, and
+// the step's rows of the output gradient in a double buffer.  A step's rows are loaded two
 // steps ahead and written to LDS behind the products of the step before it, one
 // barrier a step.  A lane reads its 8 nodes and the chunks on either side and
 // forms the five shifted operands by funnel shifts.  The rows' LDS strides are
@@ -738,19 +739,36 @@ constexpr int WG_CHUNKS_TAP = 1024; // layer 1: waves = chunks
 // takes 2 % longer, 637 -> 652 us, for the reduction's second 26 MB).
 // partial[chunk][half][dz][dy][dx][32][16 NB]
 constexpr int WG_CHUNKS = 51;  // x 5 dz: a block per compute unit
-constexpr int WG_PARTS = 2 * WG_CHUNKS;
-constexpr int WG_WAVES = 10, WG_RING = 16, WG_ROWS = 4;
+constexpr int WG_WAVES = 10, WG_RING = 16, WG_ROWS = 4, WG_STEPS = 112;
 
 // x tile of a row: 64 nodes where they divide it, else 32
 __host__ __device__ inline int wg_xt(const Geo &g) { return g.nx % 64 == 0 ? 64 : 32; }
 
-template <int NB, int XT>
+// Rows a step and chunks of a lattice.  Up to WG_STEPS four-row steps it takes
+// one row a step instead: a half of a chunk is then the longer FP32 chain, up to
+// four rows where the 64 chunks of a wave per (dz, dy) had one (on 32 x 8 x 12
+// rms 6.5e-8 against 4.9e-8; with one-row steps 3.9e-8).  One-row steps keep every
+// chain at ceil(ceil(rows / 51) / 2) <= ceil(rows / 64) rows, four-row steps from
+// 113 on (eight rows in a half against at least 452 / 64).  No more chunks than
+// steps: the reductions of up to 102 empty sums took the whole gradient of
+// 32 x 4 x 1 from 204 to 248 us.
+struct WgSplit {
+    int rs, chunks;
+};
+inline WgSplit wg_split(const Geo &g)
+{
+    const int tiles = g.nx / wg_xt(g) * g.nz;
+    const int rs = tiles * (g.ny / WG_ROWS) <= WG_STEPS ? 1 : WG_ROWS;
+    return {rs, std::min(WG_CHUNKS, tiles * (g.ny / rs))};
+}
+
+template <int NB, int XT, int RS>
 __global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks, int cout, const uint16_t *__restrict__ actT,
                                                               const uint16_t *__restrict__ gT, float *__restrict__ partial)
 {
     constexpr int SA = XT + 24, SB = XT + 8;       // row strides in elements
     constexpr int CA = XT / 8 + 2, CB = XT / 8;    // 16-byte chunks of a row
-    constexpr int T = 64 * WG_WAVES, RS = WG_ROWS;
+    constexpr int T = 64 * WG_WAVES;
     __shared__ __attribute__((aligned(16))) uint16_t s_a[WG_RING][32][SA];
     __shared__ __attribute__((aligned(16))) uint16_t s_b[2][RS][16 * NB][SB];
     // the five dz of a chunk and neighbouring chunks on one XCD: they share rows
@@ -773,13 +791,14 @@ __global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks,
     const int zcount = g.zper ? g.nz : max(0, g.nz - abs(dz));
     const int ph = g.ny / RS, steps = (g.nx / XT) * zcount * ph;
     const int p0 = (int)((int64_t)steps * chunk / chunks), p1 = (int)((int64_t)steps * (chunk + 1) / chunks);
-    // 16-byte chunks of the thread: of the step's four new input rows (halo
-    // included) and of its four output-gradient rows, at most two each
-    static_assert(RS * 32 * CA <= 2 * T && RS * 16 * NB * CB <= 2 * T, "two chunks per thread and step");
-    bool ha[2], hb[2];
-    int ac[2], arow[2], aoff[2], lao[2], boff[2], brow[2], lbo[2];
+    // 16-byte chunks of the thread: of the step's new input rows (halo included)
+    // and of its output-gradient rows, at most two each
+    constexpr int K = RS == 1 ? 1 : 2;
+    static_assert(RS * 32 * CA <= K * T && RS * 16 * NB * CB <= K * T, "K chunks per thread and step");
+    bool ha[K], hb[K];
+    int ac[K], arow[K], aoff[K], lao[K], boff[K], brow[K], lbo[K];
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
+    for (int k = 0; k < K; ++k) {
         const int q = (int)threadIdx.x + k * T, ach = (q / CA) & 31, bch = (q / CB) % cout;
         ha[k] = q < RS * 32 * CA;
         hb[k] = q < RS * cout * CB;
@@ -792,12 +811,13 @@ __global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks,
         lbo[k] = (brow[k] * 16 * NB + bch) * SB + 8 * (q % CB);
     }
     struct Rows {
-        u32x4 a[2], b[2];
+        u32x4 a[K], b[K];
     };
-    // input rows Y .. Y + 3 of layer zs (-2 <= Y < ny + 8), gradient rows y .. y + 3
+    // input rows Y .. Y + RS - 1 of layer zs (-2 <= Y < ny + 8), gradient rows
+    // y .. y + RS - 1
     auto load_a = [&](Rows &v, int x0, int zs, int Y) {
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
+        for (int k = 0; k < K; ++k)
             if (ha[k])
                 v.a[k] = *(const u32x4 *)(actT + (size_t)aoff[k] +
                                           (wrapi(x0 - 8 + 8 * ac[k], g.nx) +
@@ -805,17 +825,17 @@ __global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks,
     };
     auto load_b = [&](Rows &v, int x0, int z, int y) {
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
+        for (int k = 0; k < K; ++k)
             if (hb[k]) v.b[k] = *(const u32x4 *)(gT + (size_t)boff[k] + (x0 + g.nx * (y + g.ny * z)));
     };
     auto put_a = [&](const Rows &v, int Y) {
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
+        for (int k = 0; k < K; ++k)
             if (ha[k]) *(u32x4 *)(&s_a[0][0][0] + ((Y + arow[k]) & (WG_RING - 1)) * (32 * SA) + lao[k]) = v.a[k];
     };
     auto put_b = [&](const Rows &v, int buf) {
 #pragma unroll
-        for (int k = 0; k < 2; ++k)
+        for (int k = 0; k < K; ++k)
             if (hb[k]) *(u32x4 *)(&s_b[buf][0][0][0] + lbo[k]) = v.b[k];
     };
     int x0 = 0, z = 0, y = 0;
@@ -844,15 +864,23 @@ __global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks,
         // a run: the steps of one column that belong to the chunk
         const int n = min(p1 - p, (g.ny - y) / RS);
         const int zs = g.zper ? mod_pos(z + dz, g.nz) : z + dz;
+        // the first step's rows y - 2 .. y + RS + 1
         load_a(v0, x0, zs, y - 2);
         load_b(v0, x0, z, y);
-        load_a(v1, x0, zs, y + 2);
+        load_a(v1, x0, zs, y - 2 + RS);
         __syncthreads();  // every wave is done with the ring
         put_a(v0, y - 2);
         put_b(v0, buf);
-        put_a(v1, y + 2);
+        put_a(v1, y - 2 + RS);
+        if constexpr (RS == 1) {
+            Rows v[3];
+#pragma unroll
+            for (int k = 0; k < 3; ++k) load_a(v[k], x0, zs, y + k);
+#pragma unroll
+            for (int k = 0; k < 3; ++k) put_a(v[k], y + k);
+        }
         if (n > 1) {
-            load_a(v0, x0, zs, y + 6);
+            load_a(v0, x0, zs, y + RS + 2);
             load_b(v0, x0, z, y + RS);
         }
         __syncthreads();
@@ -862,7 +890,7 @@ __global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks,
                 half = 1;
             }
             if (i + 2 < n) {
-                load_a(v1, x0, zs, y + 10);
+                load_a(v1, x0, zs, y + 2 * RS + 2);
                 load_b(v1, x0, z, y + 2 * RS);
             }
 #pragma unroll
@@ -889,7 +917,7 @@ __global__ __launch_bounds__(64 * WG_WAVES) void k_wgrad_rows(Geo g, int chunks,
                 }
             }
             if (i + 1 < n) {
-                put_a(v0, y + 6);
+                put_a(v0, y + RS + 2);
                 put_b(v0, buf ^ 1);
                 v0 = v1;
                 __syncthreads();
@@ -1255,17 +1283,25 @@ hipError_t launch_conv_fwd(hipStream_t s, int cin, int cout, int epi, const FwdA
 size_t wgrad_partial_floats(const Geo &g, int layer)
 {
     if (layer == 1) return (size_t)row_split(g, WG_CHUNKS_TAP).chunks * 128 * 32;
-    return (size_t)WG_PARTS * NT * 32 * 16 * (layer == 2 ? 2 : 1);
+    return (size_t)2 * wg_split(g).chunks * NT * 32 * 16 * (layer == 2 ? 2 : 1);
 }
 
 template <int NB>
-void launch_wgrad_rows(hipStream_t s, const Geo &g, int cout, const uint16_t *src, const uint16_t *gT, float *partial)
+void launch_wgrad_rows(hipStream_t s, const Geo &g, const WgSplit &ws, int cout, const uint16_t *src, const uint16_t *gT,
+                       float *partial)
 {
-    const dim3 grid(5 * WG_CHUNKS), blk(64 * WG_WAVES);
-    if (wg_xt(g) == 64)
-        hipLaunchKernelGGL((k_wgrad_rows<NB, 64>), grid, blk, 0, s, g, WG_CHUNKS, cout, src, gT, partial);
-    else
-        hipLaunchKernelGGL((k_wgrad_rows<NB, 32>), grid, blk, 0, s, g, WG_CHUNKS, cout, src, gT, partial);
+    const dim3 grid(5 * ws.chunks), blk(64 * WG_WAVES);
+    const bool x64 = wg_xt(g) == 64;
+#define HSLB_WG(XT, RS) \
+    hipLaunchKernelGGL((k_wgrad_rows<NB, XT, RS>), grid, blk, 0, s, g, ws.chunks, cout, src, gT, partial)
+    if (ws.rs == 1) {
+        if (x64) HSLB_WG(64, 1);
+        else HSLB_WG(32, 1);
+    } else {
+        if (x64) HSLB_WG(64, WG_ROWS);
+        else HSLB_WG(32, WG_ROWS);
+    }
+#undef HSLB_WG
 }
 
 hipError_t launch_wgrad(hipStream_t s, int layer, const Geo &g, const uint16_t *src, const uint16_t *gT,
@@ -1277,12 +1313,13 @@ hipError_t launch_wgrad(hipStream_t s, int layer, const Geo &g, const uint16_t *
         hipLaunchKernelGGL(k_wgrad_tap_reduce, dim3(NT), dim3(256), 0, s, rs.chunks, partial, dW);
         return hipGetLastError();
     }
+    const WgSplit ws = wg_split(g);
     if (layer == 2) {
-        launch_wgrad_rows<2>(s, g, CH, src, gT, partial);
-        hipLaunchKernelGGL(k_wgrad_ch_reduce, dim3(nblocks(CH * 32 * NT)), dim3(256), 0, s, WG_PARTS, 32, CH, partial, dW);
+        launch_wgrad_rows<2>(s, g, ws, CH, src, gT, partial);
+        hipLaunchKernelGGL(k_wgrad_ch_reduce, dim3(nblocks(CH * 32 * NT)), dim3(256), 0, s, 2 * ws.chunks, 32, CH, partial, dW);
     } else {
-        launch_wgrad_rows<1>(s, g, CO, src, gT, partial);
-        hipLaunchKernelGGL(k_wgrad_ch_reduce, dim3(nblocks(CO * 32 * NT)), dim3(256), 0, s, WG_PARTS, 16, CO, partial, dW);
+        launch_wgrad_rows<1>(s, g, ws, CO, src, gT, partial);
+        hipLaunchKernelGGL(k_wgrad_ch_reduce, dim3(nblocks(CO * 32 * NT)), dim3(256), 0, s, 2 * ws.chunks, 16, CO, partial, dW);
     }
     return hipGetLastError();
 }
