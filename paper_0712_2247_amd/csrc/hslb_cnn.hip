@@ -117,27 +117,15 @@ __device__ __forceinline__ uint32_t gelu_bf16(float z)
     return f2bf(v);
 }
 
-// d GELU'(z), GELU'(z) = Phi(z) + z phi(z), in the reference form, out of line.
-__device__ __attribute__((noinline)) float dgelu_ref(float d, float z)
-{
-    return d * (phi_cdf_ref(z) + z * expf(-0.5f * z * z) * 0.39894228040143268f);
-}
-
-// bf16(d GELU'(z)).  The fast form's error is at most 2.5e-7 absolute in GELU',
-// as the reference form's is; it decides the rounding unless the value lies
-// within 64 FP32 ulps of a tie, where the reference does (about 1 value in 500).
-// Only where the two terms cancel (z near -0.75, |GELU'| below 0.04) can the two
-// forms round apart, by one unit of a value that small.  erfcf and expf on every
-// value cost the input gradients of layers 2 and 3 132 + 66 us, against 128 + 62
-// us, on 64 x 64 x 88.
+// bf16(d GELU'(z)), GELU'(z) = Phi(z) + z phi(z), in the reference form on every
+// value: the two terms cancel near z = -0.75, where the fast form's absolute error
+// (9e-8 in GELU', the reference form's 5e-8; 2.1e-7 against 1.2e-7 over all z) is no
+// multiple of the small value's last place, so that no window around the rounding
+// ties can hold it.  The fast form with such a window took 4 us each off the input
+// gradients of layers 2 and 3 (64 x 64 x 88: 132 -> 128, 66 -> 62 us).
 __device__ __forceinline__ uint32_t dgelu_bf16(float d, float z)
 {
-    float g;
-    const float p = phi_cdf_fast(z, g);
-    float v = d * fmaf(z * g, 0.39894228040143268f, p);
-    const uint32_t lo = __float_as_uint(v) & 0xFFFFu;
-    if (lo - 0x7FC0u < 0x80u || z < -13.0f) v = dgelu_ref(d, z);
-    return f2bf(v);
+    return f2bf(d * (phi_cdf_ref(z) + z * expf(-0.5f * z * z) * 0.39894228040143268f));
 }
 
 __device__ __forceinline__ bf16x8 as_bf(u32x4 v) { return __builtin_bit_cast(bf16x8, v); }
