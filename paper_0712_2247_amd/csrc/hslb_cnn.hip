@@ -121,8 +121,8 @@ __device__ __forceinline__ uint32_t gelu_bf16(float z)
 // value: the two terms cancel near z = -0.75, where the fast form's absolute error
 // (9e-8 in GELU', the reference form's 5e-8; 2.1e-7 against 1.2e-7 over all z) is no
 // multiple of the small value's last place, so that no window around the rounding
-// ties can hold it.  The fast form with such a window took 4 us each off the input
-// gradients of layers 2 and 3 (64 x 64 x 88: 132 -> 128, 66 -> 62 us).
+// ties can hold it.  Nor is it faster: with such a window the input gradients of
+// layers 2 and 3 take 106.8 + 45.8 us on 64 x 64 x 88, so 102.6 + 47.5 us.
 __device__ __forceinline__ uint32_t dgelu_bf16(float d, float z)
 {
     return f2bf(d * (phi_cdf_ref(z) + z * expf(-0.5f * z * z) * 0.39894228040143268f));
@@ -284,6 +284,21 @@ __device__ __forceinline__ size_t zfrag_at(const Geo &g, int x0, int y0, int z0,
     return (size_t)g.nx * g.ny * z0 * 32 + (((size_t)tile * 4 + w) * rows + r) * 512 + h * 256 + lane * 4;
 }
 
+// The channel-last copy of a block's 32-channel bf16 results, from ot.
+__device__ __forceinline__ void store_cl(const FwdArgs &a, const Geo &g, const uint16_t *ot, int x0, int y0, int z0,
+                                         int rows)
+{
+    constexpr int TN = TX * TY * TZ;
+    for (int q = threadIdx.x; q < TN * 4; q += 256) {
+        const int l = q >> 2, pt = q & 3;
+        const int x = l % TX, y = (l / TX) % TY, r = l / (TX * TY);
+        if (r < rows) {
+            const size_t node = (size_t)(x0 + x) + (size_t)g.nx * ((y0 + y) + (size_t)g.ny * (z0 + r));
+            *(u32x4 *)(a.out_cl + node * 32 + 8 * pt) = *(const u32x4 *)(ot + l * 32 + 8 * pt);
+        }
+    }
+}
+
 // Stores a block's 32-channel bf16 results: lane (li, lg) holds v[r][h][j] of
 // node (x0 + 4 lg + j, y0 + w, z0 + r), channel 16 h + li.  The channel-last
 // copy goes through LDS and leaves as whole 16-byte node parts; of the
@@ -313,15 +328,28 @@ __device__ __forceinline__ void store_bf16(const FwdArgs &a, const Geo &g, uint1
 #pragma unroll
             for (int j = 0; j < 4; ++j) ot[((r * TY + w) * TX + 4 * lg + j) * 32 + 16 * h + li] = (uint16_t)v[r][h][j];
     __syncthreads();
-    constexpr int TN = TX * TY * TZ;
-    for (int q = threadIdx.x; q < TN * 4; q += 256) {
-        const int l = q >> 2, pt = q & 3;
-        const int x = l % TX, y = (l / TX) % TY, r = l / (TX * TY);
-        if (r < rows) {
-            const size_t node = (size_t)(x0 + x) + (size_t)g.nx * ((y0 + y) + (size_t)g.ny * (z0 + r));
-            *(u32x4 *)(a.out_cl + node * 32 + 8 * pt) = *(const u32x4 *)(ot + l * 32 + 8 * pt);
-        }
-    }
+    store_cl(a, g, ot, x0, y0, z0, rows);
+}
+
+// GELU epilogue of a forward layer with 32 output channels outside training: only
+// the channel-last activations are wanted, and each goes to LDS as it is formed.
+// The training epilogue holds all 32 of a lane and tests its optional outputs: on
+// 64 x 64 x 136 layers 1 and 2 take 34.4 + 124.9 us with it, 31.5 + 121.8 us so.
+__device__ __forceinline__ void gelu_epilogue_cl(const FwdArgs &a, const Geo &g, uint16_t *ot,
+                                                 const f32x4 (&acc)[ROWS][2], int x0, int y0, int z0, int rows, int w,
+                                                 int li, int lg)
+{
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                ot[((r * TY + w) * TX + 4 * lg + j) * 32 + 16 * h + li] =
+                    (uint16_t)gelu_bf16(acc[r][h][j] + a.bias[16 * h + li]);
+    __syncthreads();
+    store_cl(a, g, ot, x0, y0, z0, rows);
 }
 
 // GELU epilogue of a forward layer with 32 output channels, and the GELU'
@@ -386,7 +414,7 @@ __device__ __forceinline__ void dgelu_epilogue(const FwdArgs &a, const Geo &g, u
 // ahead into a register ring; rows past the end of a partial z tile are
 // computed on the staged zeros or wrapped layers and not stored, which keeps
 // the loop free of branches.
-template <int CIN, int EPI>
+template <int CIN, int EPI, bool TRAIN>
 __global__ __launch_bounds__(256) void k_conv_fwd(FwdArgs a)
 {
     static_assert((CIN == 1 && EPI == EPI_GELU) || (CIN == 4 && EPI == EPI_DGELU),
@@ -458,8 +486,10 @@ __global__ __launch_bounds__(256) void k_conv_fwd(FwdArgs a)
     }
 
     __shared__ __attribute__((aligned(16))) uint16_t ot[TX * TY * TZ * 32];
-    if constexpr (EPI == EPI_GELU)
+    if constexpr (EPI == EPI_GELU && TRAIN)
         gelu_epilogue(a, g, ot, acc, x0, y0, z0, rows, w, li, lg);
+    else if constexpr (EPI == EPI_GELU)
+        gelu_epilogue_cl(a, g, ot, acc, x0, y0, z0, rows, w, li, lg);
     else
         dgelu_epilogue(a, g, ot, acc, x0, y0, z0, rows, w, li, lg);
 }
@@ -478,7 +508,7 @@ __global__ __launch_bounds__(256) void k_conv_fwd(FwdArgs a)
 // are issued (no register copies, no wait on a load just issued).  On the
 // 64x64x136 slit layer 2 takes 141 us (40 % of the BF16 peak; 188 us with
 // per-lane tap division and guarded loads, 249 us with the 64-byte halo).
-template <int NH, int EPI>
+template <int NH, int EPI, bool TRAIN>
 __global__ __launch_bounds__(256, 4) void k_conv_fwd_split(FwdArgs a)
 {
     static_assert(NH == 2 && (EPI == EPI_GELU || EPI == EPI_DGELU), "layer 2 forward and input gradient");
@@ -546,8 +576,10 @@ __global__ __launch_bounds__(256, 4) void k_conv_fwd_split(FwdArgs a)
     }
 
     static_assert(TX * TY * TZ * 32 <= HNODES * 16, "the block's activations fit the halo buffer");
-    if constexpr (EPI == EPI_GELU)
+    if constexpr (EPI == EPI_GELU && TRAIN)
         gelu_epilogue(a, g, tile, acc, x0, y0, z0, rows, w, li, lg);
+    else if constexpr (EPI == EPI_GELU)
+        gelu_epilogue_cl(a, g, tile, acc, x0, y0, z0, rows, w, li, lg);
     else
         dgelu_epilogue(a, g, tile, acc, x0, y0, z0, rows, w, li, lg);
 }
@@ -1245,16 +1277,19 @@ hipError_t launch_conv_fwd(hipStream_t s, int cin, int cout, int epi, const FwdA
     const int blocks = (a.g.nx / TX) * (a.g.ny / TY) * ((a.g.nz + TZ - 1) / TZ);
     const dim3 grid(blocks), blk(256);
     const int nh = cout == 32 ? 2 : 1;
+    const bool train = a.zfrag || a.out_f32 || a.out_cm || !a.out_cl;
     if (cin == 1 && nh == 2 && epi == EPI_GELU) {
-        hipLaunchKernelGGL((k_conv_fwd<1, EPI_GELU>), grid, blk, 0, s, a);
+        if (train) hipLaunchKernelGGL((k_conv_fwd<1, EPI_GELU, true>), grid, blk, 0, s, a);
+        else hipLaunchKernelGGL((k_conv_fwd<1, EPI_GELU, false>), grid, blk, 0, s, a);
         return hipGetLastError();
     }
     if (cin == 32 && nh == 2 && epi == EPI_GELU) {
-        hipLaunchKernelGGL((k_conv_fwd_split<2, EPI_GELU>), grid, blk, 0, s, a);
+        if (train) hipLaunchKernelGGL((k_conv_fwd_split<2, EPI_GELU, true>), grid, blk, 0, s, a);
+        else hipLaunchKernelGGL((k_conv_fwd_split<2, EPI_GELU, false>), grid, blk, 0, s, a);
         return hipGetLastError();
     }
     if (cin == 32 && nh == 2 && epi == EPI_DGELU) {
-        hipLaunchKernelGGL((k_conv_fwd_split<2, EPI_DGELU>), grid, blk, 0, s, a);
+        hipLaunchKernelGGL((k_conv_fwd_split<2, EPI_DGELU, true>), grid, blk, 0, s, a);
         return hipGetLastError();
     }
     if (cin == 32 && nh == 1 && epi == EPI_OUT) {
@@ -1262,7 +1297,7 @@ hipError_t launch_conv_fwd(hipStream_t s, int cin, int cout, int epi, const FwdA
         return hipGetLastError();
     }
     if (cin == 4 && nh == 2 && epi == EPI_DGELU) {
-        hipLaunchKernelGGL((k_conv_fwd<4, EPI_DGELU>), grid, blk, 0, s, a);
+        hipLaunchKernelGGL((k_conv_fwd<4, EPI_DGELU, true>), grid, blk, 0, s, a);
         return hipGetLastError();
     }
     return hipErrorInvalidValue;
