@@ -276,6 +276,13 @@ int hslb_set_graph(hslb_ctx *ctx, int32_t enable);
  * Errors: HSLB_EINVAL (null context). */
 int hslb_set_collide_tiles(hslb_ctx *ctx, int32_t enable);
 
+/* Kernels of small lattices (19 velocities, hard-sphere force on): 1 (default)
+ * lets a lattice of few nodes step through the two kernels made for them; 0 keeps
+ * the context on the kernels of large lattices, whatever its size.  Both give
+ * bitwise identical results.
+ * Errors: HSLB_EINVAL (null context). */
+int hslb_set_small_lattice(hslb_ctx *ctx, int32_t enable);
+
 /* Per-kernel timing with HIP events on the context's stream.  When enabled
  * (and graphs off), hslb_step brackets every kernel launch with events;
  * hslb_kernel_times fills names/total milliseconds/launch counts for up to

@@ -258,6 +258,13 @@ public:
         return HSLB_OK;
     }
     bool collide_tiles = false;
+    // the kernels of small lattices where their rules take the lattice
+    virtual int set_small_lattice(bool on)
+    {
+        small_lattice = on;
+        return HSLB_OK;
+    }
+    bool small_lattice = true;
     int64_t shift_every = 0;  // refresh period of the layer reference densities (0: never)
     KernelTimer kt;
 };
@@ -427,6 +434,13 @@ public:
     {
         if (on != collide_tiles) drop_graphs();  // the captured steps hold the other kernel
         collide_tiles = on;
+        return HSLB_OK;
+    }
+
+    int set_small_lattice(bool on) override
+    {
+        if (on != small_lattice) drop_graphs();
+        small_lattice = on;
         return HSLB_OK;
     }
 
@@ -621,7 +635,7 @@ public:
     {
         int rc;
         if (l39()) return one_step39();
-        const bool split = collide_split_apply(L_, sigma_, sc_, sizeof(TM));
+        const bool split = small_lattice && collide_split_apply(L_, sigma_, sc_, sizeof(TM));
         const bool small = split && fields_small_apply(L_, sigma_, sizeof(TM));
         const AttWeights *aw = sc_.phi ? &aw_ : nullptr;
         double *att_b = sc_.phi ? att_d_ + (size_t)L_.N : nullptr;
@@ -2423,6 +2437,12 @@ int hslb_set_collide_tiles(hslb_ctx *ctx, int32_t enable)
 {
     CTX_CHECK(ctx);
     return ctx->eng->set_collide_tiles(enable != 0);
+}
+
+int hslb_set_small_lattice(hslb_ctx *ctx, int32_t enable)
+{
+    CTX_CHECK(ctx);
+    return ctx->eng->set_small_lattice(enable != 0);
 }
 
 int hslb_set_kernel_timing(hslb_ctx *ctx, int32_t enable)
