@@ -662,7 +662,7 @@ public:
         if (sc_.phi && !small && (rc = attraction())) return rc;
         rc = launch("collide", [&] {
             if (split) return launch_collide_split<TF, TM>(st(), L_, sigma_, sc_, chi_d_, f_[cur_], f_[1 - cur_], fld_, aw,
-                                                           att_b);
+                                                           small ? att_b : nullptr);
             return launch_collide<TF, TM>(st(), L_, sigma_, sc_, chi_d_, f_[cur_], f_[1 - cur_], fld_, collide_tiles);
         });
         if (rc) return rc;

@@ -1578,7 +1578,7 @@ __global__ __launch_bounds__(256) void k_force(LatticeDev L, StepConst sc, const
 //                    two to four of the 19 directions.  A wave then waits for
 //                    about 30 loads instead of 127.
 // Every sum is formed in the order of the general kernels, so the results are
-// bit for bit theirs (the attraction's aside, whose potential rounds apart).
+// bit for bit theirs.
 // Kernel times (rocprofv3), before -> now: 8x8x24 sigma 4 FP64 3.6 + 2.0 + 2.2 +
 // 2.7 + collide 9.4 -> 5.1 + 4.9 us; 16x16x128 sigma 4 FP64 with the attraction
 // 4.9 + 3.4 + 3.8 + 10.4 + 14.2 -> 11.7 + 10.1 us; 24x20x30 sigma 8, the force of
@@ -1926,7 +1926,11 @@ __device__ __forceinline__ double att_phi_z(const LatticeDev &L, const AttWeight
 #pragma unroll 8
         for (int m = m0; m <= m1; ++m) s += aw.w[m] * b[(size_t)L.plane * (z + m - aw.R) + r];
     }
-    return -aw.eps * s;
+    {
+        // rounded as k_att_z stores it: not fused into the difference of two phi
+#pragma clang fp contract(off)
+        return -aw.eps * s;
+    }
 }
 
 // One direction's post-collision population as it is stored, and where (as
@@ -1960,7 +1964,12 @@ __device__ __forceinline__ Streamed<TF> stream_one(const LatticeDev &L, const St
 }
 
 // The step's collision, or (FORCE) the force alone into Fout, of 64 nodes of a
-// layer by six waves.  ATT: the attraction, from its x and y passes in att_b.
+// layer by six waves.  ATT: the attraction, from its x and y passes in att_b (the
+// fields kernel's, the pass along z is formed here) or, where att_b is null, from
+// the finished potential: six sums of 2 R + 1 terms a node cost more than the pass
+// saves (us per step, FP64, range 4, general kernels / sums / potential:
+// 24x20x30 sigma 8 33.9 / 27.4 / 25.6, 48x48x16 sigma 4 39.3 / 38.9 / 35.0,
+// 32x32x60 sigma 6 39.0 / 47.3 / 41.0).
 // Every lane takes part in the barrier; lanes past the layer's end repeat its
 // last node and store nothing.
 template <int SIG, typename SRC, typename TF, typename TM, bool MASK, bool ATT, bool FORCE>
@@ -2051,7 +2060,15 @@ __global__ __launch_bounds__(384) void k_collide_split(LatticeDev L, StepConst s
                     zm = (zm < 0) ? L.nz - 1 : zm;
                 }
             }
-            s_fa[a][lane] = -n * (att_phi_z(L, aw, att_b, rp, zp) - att_phi_z(L, aw, att_b, rm, zm)) / 2.0;
+            double pp, pm;
+            if (att_b) {
+                pp = att_phi_z(L, aw, att_b, rp, zp);
+                pm = att_phi_z(L, aw, att_b, rm, zm);
+            } else {
+                pp = sc.phi[L.plane * zp + rp];
+                pm = sc.phi[L.plane * zm + rm];
+            }
+            s_fa[a][lane] = -n * (pp - pm) / 2.0;
         }
     }
     __syncthreads();

@@ -13,7 +13,7 @@ import pytest
 import oracle
 from paper_0712_2247_amd import hslb, workloads
 
-from . import test_gpu_masks, test_gpu_parity
+from . import test_gpu_attraction, test_gpu_masks, test_gpu_parity
 
 pytestmark = pytest.mark.gpu
 
@@ -105,3 +105,51 @@ def test_steps_over_a_refresh_of_the_reference_tables(shape, graph):
     a = advance(*shape, "f32", n, u, 23, small=True, period=5, graph=graph)
     b = advance(*shape, "f32", n, u, 23, small=False, period=5, graph=graph)
     assert np.array_equal(a[0], b[0]) and np.array_equal(a[1][0], b[1][0]) and np.array_equal(a[1][1], b[1][1])
+
+
+ATTRACTION = [  # nx, ny, nz, sigma, walls, range, mask: with and without the fields kernel, axes the range wraps over
+    (16, 16, 20, 4, 0, 4.0, False), (13, 12, 16, 3, 2, 2.0, False), (6, 8, 9, 3, 0, 10.0, False),
+    (24, 20, 30, 8, 4, 3.0, False), (32, 32, 24, 6, 0, 4.0, False), (16, 16, 12, 8, 0, 10.0, False),
+    (12, 10, 18, 4, 2, 2.5, True), (20, 22, 24, 6, 3, 2.5, True), (64, 10, 20, 4, 2, 3.0, False),
+]
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("case", ATTRACTION, ids=lambda c: "x".join(map(str, c)))
+def test_attraction(case, precision):
+    """Both ways bit for bit, and in FP64 against the oracle."""
+    nx, ny, nz, sigma, walls, reach, masked = case
+    print(f"case {case} {precision}", flush=True)
+    n, u = workloads.random_state((nz, ny, nx), workloads.number_density(0.2, sigma), 0.05, 2e-3, seed=nx + nz,
+                                  solid_lo=walls, solid_hi=walls)
+    m = None
+    if masked:
+        m = np.zeros((nz, ny, nx), dtype=np.uint8)
+        m[nz // 2 - 1:nz // 2 + 1, 2:5, 3:6] = 1
+        n, u = n * (m == 0), u * (m == 0)
+    kw = dict(att_eps=2e-3, att_range=reach)
+    args = (nx, ny, nz, sigma, walls, precision, n, u, 12)
+    f, (gn, gu) = advance(*args, mask=m, **kw)
+    fs, (sn, su) = advance(*args, mask=m, small=True, **kw)
+    assert np.array_equal(f, fs) and np.array_equal(gn, sn) and np.array_equal(gu, su)
+    if precision == "f64":
+        o = oracle.Oracle(nx, ny, nz, sigma=sigma, tau=0.9, accel=(1e-5, 2e-6, 0.0), wall_lo=walls, wall_hi=walls, **kw)
+        if masked:
+            o.set_solid(m)
+        o.init(n, u)
+        o.step(12)
+        assert rel(f, o.get_populations()) <= 1e-13
+
+
+@pytest.mark.parametrize("case", test_gpu_attraction.CASES, ids=lambda c: "x".join(map(str, c[:6])))
+def test_attraction_on_the_general_kernels(case):
+    """The attraction's step cases, at the bar they have there."""
+    print(f"case {case}", flush=True)
+    n, u = test_gpu_attraction._state(case, seed=12)
+    g, o = test_gpu_attraction._pair(case, accel=(1e-5, 0.0, 0.0))
+    hslb.hslb_set_small_lattice(g.ctx, False)
+    g.init(n, u)
+    o.init(n, u)
+    g.step(30)
+    o.step(30)
+    assert rel(g.get_populations(), o.get_populations()) <= 1e-13
