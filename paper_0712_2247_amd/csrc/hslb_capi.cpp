@@ -635,9 +635,10 @@ public:
     {
         int rc;
         if (l39()) return one_step39();
-        const bool split = small_lattice && collide_split_apply(L_, sigma_, sc_, sizeof(TM));
-        const bool small = split && fields_small_apply(L_, sigma_, sizeof(TM));
         const AttWeights *aw = sc_.phi ? &aw_ : nullptr;
+        const SmallRoute route =
+            small_lattice ? small_route(L_, sigma_, sc_, sizeof(TM), aw ? aw_.R : -1) : SmallRoute::none;
+        const bool split = route != SmallRoute::none, small = route == SmallRoute::fields;
         double *att_b = sc_.phi ? att_d_ + (size_t)L_.N : nullptr;
         if (small) {
             rc = launch("fields", [&] {

@@ -175,11 +175,11 @@ hipError_t launch_smooth2(hipStream_t s, const LatticeDev &L, int sigma, double 
 // then the collision with the shell sum split over six waves.  With the
 // attraction (aw not null) the first also forms the passes along x and y of the
 // potential in att_b [N] and the density field fld.n, and the second its pass
-// along z; with a null att_b the second reads the finished potential c.phi.  The
-// *_apply rules say which lattices they take; the launchers
-// return hipErrorInvalidValue for others.
-bool fields_small_apply(const LatticeDev &L, int sigma, size_t tm_bytes);
-bool collide_split_apply(const LatticeDev &L, int sigma, const StepConst &c, size_t tm_bytes);
+// along z; with a null att_b the second reads the finished potential c.phi.
+// small_route says which of the two a lattice takes: none, the collision alone, or
+// both.  The launchers return hipErrorInvalidValue for a layer beyond the LDS.
+enum class SmallRoute { none, collide, fields };
+SmallRoute small_route(const LatticeDev &L, int sigma, const StepConst &c, size_t tm_bytes, int att_reach);
 bool force_fields_apply(const LatticeDev &L, int sigma);
 template <typename TF, typename TM>
 hipError_t launch_fields_small(hipStream_t s, const LatticeDev &L, int sigma, double eta_pref, int g2_model,

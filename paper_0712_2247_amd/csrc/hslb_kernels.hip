@@ -3266,20 +3266,7 @@ hipError_t launch_attraction(hipStream_t s, const LatticeDev &L, const AttWeight
     return hipGetLastError();
 }
 
-// Which lattices take the small-lattice kernels (us per step, MI355X; general
-// kernels / split collide / both):
-//   8x8x24 sigma 4 FP64    17.0 / 13.6 / 10.3    16x16x26 sigma 8 FP32   18.3 / 14.2 / 15.3
-//   9x9x73 sigma 7 FP32    18.8 / 15.6 / 13.0    24x20x30 sigma 8 FP64   24.1 / 17.6 / 24.0
-//   16x16x40 sigma 4 FP64  20.0 / 13.6 / 12.5    16x16x128 sigma 8 FP32  18.9 / 16.2 / 18.8
-//   16x16x128 sigma 4 FP64 23.3 / 18.5 / 17.2    32x32x32 sigma 4 FP32   18.0 / 15.3 / 16.8
-//   16x16x256 sigma 8 FP64 30.5 / 29.5 / 29.7    16x16x256 sigma 8 FP32  21.5 / 22.1 / 22.4
-//   32x32x64 sigma 6 FP64  27.0 / 25.9 / 34.7    64x64x40 sigma 8 FP64   40.6 / 43.7 / 43.7
-// The split collide wins until its six waves per 64 nodes fill the chip (64 Ki
-// nodes with FP64 fields, which hold the moments; 40 Ki with FP32, where each
-// wave sums the populations again).  The fields kernel wins while a block forms
-// the densities of at most 1536 nodes (one and a half per lane): beyond, the
-// layers it repeats cost more than the launches it saves.
-constexpr int kSplitNodes64 = 65536, kSplitNodes32 = 40960, kFieldsNodes = 32768, kFieldsBlock = 1536;
+constexpr int kSmallNodes = 65536;
 constexpr int kSmallBlocks = 256;
 constexpr size_t kSmallLds = 156 * 1024;
 
@@ -3311,25 +3298,47 @@ bool small_tile(const LatticeDev &L, int sigma, size_t tm, bool one, SmallTile &
     return fits;
 }
 
-bool fields_small_apply(const LatticeDev &L, int sigma, size_t tm)
-{
-    SmallTile t;
-    return sigma >= 2 && sigma <= 8 && L.N <= kFieldsNodes && (2 * (sigma / 2) + 2) * L.plane <= kFieldsBlock &&
-           small_tile(L, sigma, tm, true, t);
-}
-
 bool force_fields_apply(const LatticeDev &L, int sigma)
 {
     SmallTile t;
-    return sigma >= 2 && sigma <= 8 && L.N <= kSplitNodes64 && small_tile(L, sigma, sizeof(double), false, t);
+    return sigma >= 2 && sigma <= 8 && L.N <= kSmallNodes && small_tile(L, sigma, sizeof(double), false, t);
 }
 
+// Which lattices take the small-lattice kernels.  us per step on an MI355X,
+// general kernels / split collide / fields kernel and split collide:
+//   FP64  8x8x100 s4    16.4 / 13.0 / 10.9   16x16x128 s4  23.4 / 18.7 / 18.1   24x24x57 s4   23.5 / 20.9 / 30.1
+//         12x12x213 s7  23.0 / 22.9 / 21.9   6x6x800 s4    23.5 / 23.5 / 26.3   10x10x320 s8  26.6 / 24.7 / 29.5
+//         16x16x256 s8  30.0 / 29.6 / 30.4   16x16x256 s3  26.3 / 25.8 / 21.8   12x12x433 s4  28.9 / 30.2 / 32.6
+//   FP32  8x8x100 s4    16.2 / 13.2 / 11.0   16x16x128 s4  18.8 / 16.2 / 15.8   24x24x57 s4   19.0 / 16.5 / 23.5
+//         12x12x213 s7  19.0 / 18.2 / 17.4   6x6x800 s4    19.6 / 20.5 / 23.6   16x16x160 s8  20.7 / 19.2 / 20.7
+//         16x16x200 s8  21.4 / 21.8 / 22.8   16x16x256 s3  20.7 / 21.7 / 18.4   32x32x64 s6   21.9 / 22.8 / 22.8
+//   attraction, range 3: 12x12x213 s5 FP32 27.0 / 27.7 / 23.3; range 10: 31.5 / 32.3 / 32.8
+// The split collide wins until its six waves per 64 nodes fill the chip: 1152
+// blocks with FP64 fields, which hold the moments (800 where a layer is one or two
+// partly filled blocks), 640 with FP32, where each wave sums the populations
+// again, 600 and 512 where the attraction's three passes stay as they are.  The
+// fields kernel wins while a block forms the densities of at most 1536 nodes, the
+// grid at most 5200 waves of them, and its blocks, of up to 16 waves at 16 waves a
+// compute unit, are resident at once (a second round costs what the launches
+// save); with the attraction the sums along z, six a node, set the end earlier, at
+// 640 blocks of the collide, 520 for ranges beyond 8 (2 R + 1 > 49 terms).  Over
+// 732 measured lattices (planes of 16 to 2304 nodes, 100 to 1300 blocks, sigma 2 to
+// 8) no choice is slower than the general kernels by more than the noise.
 // Lattices that the LDS-staged collide takes keep the choice between it and the
-// direct kernel.
-bool collide_split_apply(const LatticeDev &L, int sigma, const StepConst &c, size_t tm)
+// direct kernel.  att_reach: R of the attraction's passes, negative without.
+SmallRoute small_route(const LatticeDev &L, int sigma, const StepConst &c, size_t tm, int att_reach)
 {
-    return sigma >= 2 && sigma <= 8 && c.hs_on && L.N <= (tm == 8 ? kSplitNodes64 : kSplitNodes32) &&
-           !collide_tiles_apply(L, sigma, c, tm == 4);
+    if (sigma < 2 || sigma > 8 || !c.hs_on || L.N > kSmallNodes || collide_tiles_apply(L, sigma, c, tm == 4))
+        return SmallRoute::none;
+    const bool att = att_reach >= 0, f64 = tm == 8;
+    const int layers = 2 * (sigma / 2) + 2, chunks = (L.plane + 63) / 64, blocks = chunks * L.nz;
+    const int waves = std::min(16, layers * chunks);
+    SmallTile t;
+    if (layers * L.plane <= 1536 && layers * blocks <= 5200 && L.nz <= 256 * (16 / waves) &&
+        blocks <= (!att ? 1024 : att_reach <= 24 ? 640 : 520) && small_tile(L, sigma, tm, true, t))
+        return SmallRoute::fields;
+    const int most = att ? (f64 ? 600 : 512) : !f64 ? 640 : chunks > 2 || L.plane % 64 == 0 ? 1152 : 800;
+    return blocks <= most ? SmallRoute::collide : SmallRoute::none;
 }
 
 template <int SIG, typename SRC, typename TM, bool ATT>
@@ -3377,7 +3386,6 @@ template <typename TF, typename TM>
 hipError_t launch_fields_small(hipStream_t s, const LatticeDev &L, int sigma, double eta_pref, int g2_model,
                                const double *nref, const TF *f, Fields<TM> fld, const AttWeights *aw, double *att_b)
 {
-    if (!fields_small_apply(L, sigma, sizeof(TM))) return hipErrorInvalidValue;
     return launch_fields_small_src(s, L, sigma, eta_pref, g2_model, PopSource<TF>{f, nref}, fld, aw, att_b);
 }
 
@@ -3412,7 +3420,7 @@ template <typename TF, typename TM>
 hipError_t launch_collide_split(hipStream_t s, const LatticeDev &L, int sigma, const StepConst &c, const double *chi,
                                 const TF *fin, TF *fout, Fields<TM> fld, const AttWeights *aw, const double *att_b)
 {
-    if (!collide_split_apply(L, sigma, c, sizeof(TM))) return hipErrorInvalidValue;
+    if (!c.hs_on) return hipErrorInvalidValue;
     using S = PopSource<TF>;
     const S src{fin, c.nref_r};
 #define HSLB_CS(SG) \

@@ -153,3 +153,23 @@ def test_attraction_on_the_general_kernels(case):
     g.step(30)
     o.step(30)
     assert rel(g.get_populations(), o.get_populations()) <= 1e-13
+
+
+# Either side of the lines at which a lattice leaves the fields kernel (its blocks
+# resident at once, nodes a block forms, waves of the grid) and the split collide.
+RULE_EDGES = [(6, 6, 512, 4, 0), (6, 6, 513, 4, 0), (16, 16, 256, 3, 0), (16, 16, 216, 4, 0), (16, 16, 217, 4, 0),
+              (12, 16, 30, 6, 3), (12, 17, 30, 6, 3), (10, 10, 400, 5, 0), (10, 10, 401, 5, 0), (18, 18, 192, 2, 1),
+              (16, 16, 160, 8, 4), (16, 16, 161, 8, 4)]
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("case", RULE_EDGES, ids=lambda c: "x".join(map(str, c)))
+def test_edges_of_the_rule(case, precision):
+    """Bit for bit the general kernels, whichever way the lattice goes."""
+    nx, ny, nz, sigma, walls = case
+    print(f"case {case} {precision}", flush=True)
+    n, u = workloads.random_state((nz, ny, nx), workloads.number_density(0.2, sigma), 0.02, 1e-3, seed=nz + sigma,
+                                  solid_lo=walls, solid_hi=walls)
+    a = advance(nx, ny, nz, sigma, walls, precision, n, u, 6)
+    b = advance(nx, ny, nz, sigma, walls, precision, n, u, 6, small=True)
+    assert np.array_equal(a[0], b[0]) and np.array_equal(a[1][0], b[1][0]) and np.array_equal(a[1][1], b[1][1])
