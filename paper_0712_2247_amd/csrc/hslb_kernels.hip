@@ -1481,14 +1481,12 @@ __device__ __forceinline__ void collide_block(const LatticeDev &L, const StepCon
     if (r < L.plane) d_collide<SIG, !NT, TF, TM, MASK, NT, false, ROT>(L, sc, chi, fin, fout, fld, z, r);
 }
 
-// The kernel proper, capped at 128 registers (the attribute counts them in
-// pairs), so that 4 waves share a SIMD: scheduled for 3 waves it takes 128 to
-// 138 otherwise, and which side of 128 it falls on decides 4 waves or 3.  The
-// cap costs up to 6 spilled registers; scheduling for 4 waves (104 to 122
-// registers, its loads closer to their uses) is slower than either.  Per step:
-// 100x72x90 slit FP32 72.3 -> 70.3 us, 64x64x136 slit with FP64 storage
-// 116.8 -> 109.0 us, 256^3 bulk 1942 -> 1935 us.  The cache-resident FP64
-// instances lose (100x60x40 56.7 -> 57.9 us) and go without (k_collide_free).
+// The kernel proper, capped at 128 registers (the attribute counts them in pairs)
+// so that 4 waves share a SIMD, and without the cap (k_collide_free): scheduled for
+// 3 waves the instances take 124 to 166 registers, and which side of 128 they fall
+// on decides 4 waves or 3.  The cap costs up to 11 spilled registers (see
+// collide_capped); scheduling for 4 waves (104 to 122 registers, its loads closer
+// to their uses) is slower than either.
 template <int SIG, typename TF, typename TM, bool MASK, bool NT, int ROT>
 __global__ __launch_bounds__(256, HSLB_COLLIDE_WAVES) __attribute__((amdgpu_num_vgpr(64))) void k_collide(
     LatticeDev L, StepConst sc, const double *__restrict__ chi, const TF *__restrict__ fin, TF *__restrict__ fout,
@@ -3811,14 +3809,31 @@ hipError_t launch_collide(hipStream_t s, const LatticeDev &L, int sigma, const S
     return launch_collide_t<TF, TM, false, false>(s, sigma, g, b, L, c, chi, fin, fout, fld, cpp, band);
 }
 
+// Which collide instances are capped at 128 registers (us per step free / capped;
+// rot: how lanes share reads, see lane_x):
+//   FP32, in the cache, rot 0   100x100x60 s2 to s8   64.6 / 62.0 to 68.7 / 67.2
+//                       rot 1   64x64x189 s8          73.5 / 74.4 (128 registers free)
+//         beyond, rot 0         100x100x200 s2, s7    190 / 202, 214 / 223; s5 201.6 / 201.6
+//                 rot 1         64x64x480 s2, s4      160 / 181, 170 / 161; s8 191 / 189
+//                 rot 3         128x128x160 s2, s3    260 / 282, 267 / 246; s8 290 / 274
+//         solid mask            100x72x90 s2 to s8    71.9 / 70.8 to 85.0 / 82.2
+//   FP64, in the cache          100x60x40 s8          56.7 / 57.9
+//         beyond, rot 0         100x100x60 s2 to s8   128 / 126 to 131 / 127
+//                 rot 1         64x64x136 s3, s4      99.4 / 106.2, 101.2 / 98.7; s8 111 / 102
+// The losers spill 4 to 11 registers in a kernel that streams its populations.
+constexpr bool collide_capped(int sigma, bool f32, bool mask, bool nt, int rot)
+{
+    if (!f32) return nt && (rot == 0 || sigma >= 4);
+    return nt ? rot != 0 && sigma >= 3 : mask || rot == 0;
+}
+
 template <typename TF, typename TM, bool M, bool NT, int ROT>
 hipError_t launch_collide_t(hipStream_t s, int sigma, dim3 g, dim3 b, const LatticeDev &L, const StepConst &c,
                             const double *chi, const TF *fin, TF *fout, Fields<TM> fld, int cpp, int band)
 {
-    constexpr bool cap = sizeof(TF) == 4 || NT;  // see k_collide
 #define HSLB_CO(SG)                                                                                                    \
     case SG:                                                                                                           \
-        if constexpr (cap)                                                                                             \
+        if constexpr (collide_capped(SG, sizeof(TF) == 4, M, NT, ROT))                                                 \
             hipLaunchKernelGGL((k_collide<SG, TF, TM, M, NT, ROT>), g, b, 0, s, L, c, chi, fin, fout, fld, cpp, band); \
         else                                                                                                           \
             hipLaunchKernelGGL((k_collide_free<SG, TF, TM, M, NT, ROT>), g, b, 0, s, L, c, chi, fin, fout, fld, cpp,   \
