@@ -3349,7 +3349,10 @@ hipError_t launch_fields_small_t(hipStream_t s, const LatticeDev &L, double eta_
     const size_t lds = fields_small_lds(SIG, nodes, sizeof(TM));
     auto kern = k_fields_small<SIG, SRC, TM, ATT>;
     if (lds > 64 * 1024) {
-        const hipError_t e = hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        // one value for every lattice: contexts on other threads and captured steps
+        // rely on it too
+        const hipError_t e =
+            hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kSmallLds);
         if (e != hipSuccess) return e;
     }
     const int waves = std::min(16, (2 * (SIG / 2) + 2) * ((nodes + 63) / 64));

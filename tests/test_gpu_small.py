@@ -82,3 +82,33 @@ def test_force_of_device_fields(case):
                             torch.cuda.current_stream(dev).cuda_stream)
     got = F_d.cpu().numpy().reshape(want.shape)
     assert np.abs(got - want).max() <= 1e-13 * np.abs(want).max()
+
+
+def test_force_captured_beside_calls_of_another_size():
+    """A captured force call whose block takes 83 KiB of LDS, replayed after calls
+    of a lattice that takes 75 KiB: each replay gives the eager call's force."""
+    dev = torch.device("cuda:0")
+    calls = []
+    for nx, ny, nz, sigma, walls in ((24, 20, 30, 8, 4), (20, 20, 40, 8, 4)):
+        n, u = workloads.random_state((nz, ny, nx), workloads.number_density(0.25, sigma), 0.05, 3e-3, seed=nx,
+                                      solid_lo=walls, solid_hi=walls)
+        p = hslb.make_params(nx, ny, nz, sigma, 0.9, accel=(1e-5, 0.0, 0.0), wall_lo=walls, wall_hi=walls)
+        calls.append((p, torch.from_numpy(n.ravel()).to(dev), torch.from_numpy(u.ravel()).to(dev),
+                      torch.zeros(3 * n.size, dtype=torch.float64, device=dev)))
+
+    def force(k):
+        p, n, u, F = calls[k]
+        hslb.hslb_force_noalloc(p, n.data_ptr(), u.data_ptr(), F.data_ptr(), torch.cuda.current_stream(dev).cuda_stream)
+        return F
+
+    want = force(0).clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        force(0)
+    for _ in range(3):
+        force(1)
+        calls[0][3].zero_()
+        torch.cuda.synchronize(dev)
+        graph.replay()
+        torch.cuda.synchronize(dev)
+        assert torch.equal(calls[0][3], want)
