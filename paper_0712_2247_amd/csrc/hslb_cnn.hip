@@ -355,8 +355,8 @@ __device__ __forceinline__ void gelu_epilogue_cl(const FwdArgs &a, const Geo &g,
 // GELU epilogue of a forward layer with 32 output channels, and the GELU'
 // epilogue of an input gradient, on the sums acc[r][h][j] held as v above.
 // 64 x 64 x 88 in training, where the pre-activations are kept and both copies
-// written: layer 1 43 -> 37 us, layer 2 111 -> 106 us, input gradients of layer 2
-// 128 -> 111 us and of layer 3 62 -> 46 us (before, the pre-activations moved as
+// written: layer 1 44 -> 36 us, layer 2 104 -> 101 us, input gradients of layer 2
+// 120 -> 103 us and of layer 3 62 -> 48 us (before, the pre-activations moved as
 // single words and the copies as single bf16 values).
 __device__ __forceinline__ void gelu_epilogue(const FwdArgs &a, const Geo &g, uint16_t *ot, const f32x4 (&acc)[ROWS][2],
                                               int x0, int y0, int z0, int rows, int w, int li, int lg)

@@ -2029,14 +2029,14 @@ __global__ __launch_bounds__(384) void k_collide_split(LatticeDev L, StepConst s
         c.u[2] = u[2];
         c.ckap = (MASK && sc.chi_n ? sc.chi_n[id] : chi[z]) * sc.kappa;
         const double alpha[4] = {sc.alpha[0], sc.alpha[1], sc.alpha[2], sc.alpha[3]};
-#define HSLB_PART(W, P) s_part[P][lane] = shell_part<SIG, P>(fld, L, c, alpha)
+#define HSLB_PART(P) s_part[P][lane] = shell_part<SIG, P>(fld, L, c, alpha)
         switch (w) {
-        case 0: HSLB_PART(0, 3); break;
-        case 1: HSLB_PART(1, 4); HSLB_PART(1, 0); break;
-        case 2: HSLB_PART(2, 5); break;
-        case 3: HSLB_PART(3, 6); HSLB_PART(3, 1); break;
-        case 4: HSLB_PART(4, 7); break;
-        default: HSLB_PART(5, 8); HSLB_PART(5, 2); break;
+        case 0: HSLB_PART(3); break;
+        case 1: HSLB_PART(4); HSLB_PART(0); break;
+        case 2: HSLB_PART(5); break;
+        case 3: HSLB_PART(6); HSLB_PART(1); break;
+        case 4: HSLB_PART(7); break;
+        default: HSLB_PART(8); HSLB_PART(2); break;
         }
 #undef HSLB_PART
     }
@@ -3806,7 +3806,9 @@ hipError_t launch_collide(hipStream_t s, const LatticeDev &L, int sigma, const S
     // a wave per x-row of 64 nodes: x-neighbour (n, j) reads shared between
     // lanes (benchmark slit 39.9 -> 36.7 us; per step, with a solid cylinder 71
     // -> 66 us, FP64 storage 116.5 -> 108.8 us, 64x64x400 FP32 157 -> 151 us; the
-    // thermal 39-velocity collide lost from it, 110 -> 119 us)
+    // thermal 39-velocity collide lost from it, 110 -> 119 us).  Under a mask or in
+    // FP64 rows of 16, 32, 128 and 256 nodes load every corner: sharing there has
+    // not been measured.
     if (L.nx == 64)
         return launch_collide_t<TF, TM, false, false, 1>(s, sigma, g, b, L, c, chi, fin, fout, fld, cpp, band);
     return launch_collide_t<TF, TM, false, false>(s, sigma, g, b, L, c, chi, fin, fout, fld, cpp, band);
